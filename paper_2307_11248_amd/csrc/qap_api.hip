@@ -41,16 +41,22 @@ std::vector<int32_t> enumerate_tiles(int n, int rows, int *ninterior) {
     return inner;
 }
 
-int pack_instance(const int32_t *F, const int32_t *D, int n, std::vector<uint8_t> &pack, int *sym) {
+int pack_instance(const int32_t *F, const int32_t *D, int n, std::vector<uint8_t> &pack, int *sym, int *blk) {
+    int32_t loF = F[0], hiF = F[0], loD = D[0], hiD = D[0];
+    for (size_t i = 0; i < (size_t)n * n; ++i) {
+        loF = std::min(loF, F[i]); hiF = std::max(hiF, F[i]);
+        loD = std::min(loD, D[i]); hiD = std::max(hiD, D[i]);
+    }
+    if (std::min(loF, loD) < 0 || std::max(hiF, hiD) > 255) return QAP_E_RANGE;
     bool symF = true, symD = true;
     for (int i = 0; i < n; ++i)
-        for (int j = 0; j < n; ++j) {
-            const int32_t f = F[(size_t)i * n + j], d = D[(size_t)i * n + j];
-            if (f < 0 || f > 255 || d < 0 || d > 255) return QAP_E_RANGE;
-            if (f != F[(size_t)j * n + i]) symF = false;
-            if (d != D[(size_t)j * n + i]) symD = false;
+        for (int j = 0; j < i; ++j) {
+            if (F[(size_t)i * n + j] != F[(size_t)j * n + i]) symF = false;
+            if (D[(size_t)i * n + j] != D[(size_t)j * n + i]) symD = false;
         }
     *sym = (symF && symD) ? 1 : 0;
+    const int spanF = hiF - loF, spanD = hiD - loD;
+    *blk = std::min(spanF, spanD) > 127 ? 0 : (spanF <= spanD ? 1 : 2);
     const int rs = row_stride(n);
     pack.assign((size_t)4 * n * rs, 0);
     for (int i = 0; i < n; ++i)
@@ -102,6 +108,7 @@ using namespace qaph;
 
 struct qap_ctx {
     int n = 0, m = 0, sym = 0, device = 0;
+    int blk = 0;                     // of pack_instance: whether the block form's limbs hold its entries
     size_t max_smem = 0;
     uint8_t *d_mats = nullptr;       // [F | F^T | D | D^T] u8, n rows of row_stride(n) bytes
     TileSet tiles[kShapes];          // one per entry of kRowsChoices
@@ -109,8 +116,9 @@ struct qap_ctx {
     // the streamed kernel, -1 when no kernel serves this n
     int rows_choice[3] = {0, 0, 0};
     int rows_default[3] = {0, 0, 0};
-    // tabu and 2opt: the shape is picked per launch (launch_shape) until one is set
-    int auto_rows[2] = {1, 1};
+    // tabu and 2opt: the shape is picked per launch (launch_shape) until one is set; in all
+    // three the block form runs what it serves until one is set
+    int auto_rows[3] = {1, 1, 1};
     int cus = 0;                     // compute units of the device
     int blocks_cache[2][kShapes];    // workgroups per compute unit per shape, -1 = not asked yet
     int stream_ok = 0;               // the streamed kernel serves this n
@@ -192,6 +200,11 @@ int launch_shape(qap_ctx *h, int algo, int k) {
     return best >= 0 ? best : h->rows_choice[algo];
 }
 
+// Whether a tabu (algo 0, 2) or 2opt (1) search of this instance runs in block form: no
+// tile shape is set, and the block form serves it.
+bool use_block(const qap_ctx *h, int algo, int lo, int hi) {
+    return h->auto_rows[algo] && block_ok(h->n, h->sym, h->blk, algo != 1, lo, hi, h->max_smem);
+}
 
 // RAII device buffer for the blocking entry points.
 struct DevBuf {
@@ -218,6 +231,7 @@ SearchArgs base_args(const qap_ctx *h, int ri) {
     a.ntiles = ts.ntiles;
     a.ninterior = ts.ninterior;
     a.sym = h->sym;
+    a.blk = h->blk;
     return a;
 }
 
@@ -266,6 +280,14 @@ hipError_t launch_searches(qap_ctx *h, int algo, int32_t *d_perms, const int32_t
     a.trace = d_trace;
     a.trace_cap = trace_cap;
     hipError_t e = hipSuccess;
+    if (!d_freq && use_block(h, algo, lo, hi)) {
+        const size_t smem = block_smem_bytes(h->n, h->sym, hi, algo == 0);
+        for (int j = 0; j < (plain ? k : 1) && e == hipSuccess; ++j) {
+            a.job0 = j;
+            e = launch_block(algo == 0, h->n, h->sym, smem, &a, nullptr, plain ? 1 : k, st);
+        }
+        return e;
+    }
     if (d_freq && attr == 2) {
         // the unit-location table of every search, in stream-ordered scratch
         e = report(hipMallocAsync((void **)&a.uloc, (size_t)k * h->n * h->n * sizeof(int32_t) + 16, st),
@@ -329,6 +351,9 @@ int run_search(qap_ctx *h, int algo, int32_t *d_perms, int k, int iters, int lo,
     if (h->rows_choice[algo] < 0) return QAP_E_UNSUPPORTED;
     if (k == 0) return QAP_OK;
     int32_t *d_table = nullptr;
+    if (!d_freq && use_block(h, algo, lo, hi))   // makes its first neighbourhood itself
+        return dev_err(launch_searches(h, algo, d_perms, nullptr, k, iters, lo, hi, seed, start_base, d_cost, d_steps,
+                                       st, plain));
     int rc = make_tables(h, d_perms, k, &d_table, st);
     if (rc != QAP_OK) return rc;
     hipError_t e = launch_searches(h, algo, d_perms, d_table, k, iters, lo, hi, seed, start_base, d_cost,
@@ -396,6 +421,9 @@ struct WideTable {
     long long perm_off, table_off;
 };
 
+// Kernel variants of a batch: the tile shapes, then the block form by (block_nb, sym).
+constexpr int GV_COUNT = BV_COUNT + 2 * BLOCK_MAX_NB;
+
 struct qap_batch {
     int count = 0;                  // searches (items)
     long long perm_ints = 0, table_ints = 0, tile_int4 = 0;
@@ -407,19 +435,22 @@ struct qap_batch {
     // (offsets into the run's starts and the plan's tables); the matrix-core table kernel
     // takes every other item
     std::vector<WideTable> wide_tables;
-    // items are grouped by kernel variant (tile shape); one launch per non-empty group
-    int group_begin[BV_COUNT] = {}, group_count[BV_COUNT] = {};
-    size_t group_smem[BV_COUNT] = {};
+    // items are grouped by kernel variant: the tile shapes, then the block form's kernels
+    // (one per (block_nb, sym)); one launch per non-empty group
+    int group_begin[GV_COUNT] = {}, group_count[GV_COUNT] = {};
+    size_t group_smem[GV_COUNT] = {};
+    int narrow = 0;                 // items of the tile shapes up to WIDE_N (they come first)
+    int tile_count[BV_COUNT] = {};  // searches per tile shape, reported by qap_batch_groups
     // The groups run on `nlanes` side streams forked from the caller's stream, the groups
     // of one lane back to back: lane_groups[lane_begin[l] .. lane_begin[l + 1]).  Streams
     // beyond the device's hardware queues would share queues, and kernels on one queue
     // run in order, so there are at most as many lanes as free queues; the groups are
     // dealt to them by estimated work, largest first, each to the least loaded lane.
     int nlanes = 0;
-    int lane_begin[BV_COUNT + 1] = {};
-    int lane_groups[BV_COUNT] = {};
-    hipStream_t side[BV_COUNT] = {};
-    hipEvent_t ev_fork = nullptr, ev_join[BV_COUNT] = {};
+    int lane_begin[GV_COUNT + 1] = {};
+    int lane_groups[GV_COUNT] = {};
+    hipStream_t side[GV_COUNT] = {};
+    hipEvent_t ev_fork = nullptr, ev_join[GV_COUNT] = {};
     // plans made by qap_batch_create_freq: every search keeps its frequency memory (and may
     // diversify or use a unit attribute); all run in one launch of batch_freq_kernel
     bool freq_mode = false;
@@ -431,7 +462,9 @@ struct qap_batch {
 
 namespace {
 
-int item_variant(const Item &it) { return batch_variant(it.n, it.rows, it.stream != 0, it.ntiles, it.sym); }
+int tile_variant(const Item &it) { return batch_variant(it.n, it.rows, it.stream != 0, it.ntiles, it.sym); }
+int block_variant(int n, int sym) { return BV_COUNT + 2 * (block_nb(n) - 1) + sym; }
+int item_variant(const Item &it) { return it.blk ? block_variant(it.n, it.sym) : tile_variant(it); }
 
 // ---- fixed scratch of qap_tabu_noalloc_async: one array per GPU, held until the process
 //      ends.  Host code never passes the array's name to a kernel (on the host it only
@@ -486,14 +519,15 @@ int qap_create(const int32_t *F, const int32_t *D, int32_t n, qap_handle *out) {
     if (!F || !D || !out || n < 2 || n > QAP_NMAX) return QAP_E_INVALID;
     *out = nullptr;
     std::vector<uint8_t> pack;
-    int sym = 0;
-    const int prc = pack_instance(F, D, n, pack, &sym);
+    int sym = 0, blk = 0;
+    const int prc = pack_instance(F, D, n, pack, &sym, &blk);
     if (prc != QAP_OK) return prc;
     qap_ctx *h = new (std::nothrow) qap_ctx;
     if (!h) return QAP_E_NOMEM;
     h->n = n;
     h->m = n * (n - 1) / 2;
     h->sym = sym;
+    h->blk = blk;
     if (hipGetDevice(&h->device) != hipSuccess) { delete h; return QAP_E_DEVICE; }
     int smem = 0;
     if (hipDeviceGetAttribute(&smem, hipDeviceAttributeMaxSharedMemoryPerBlock, h->device) != hipSuccess) {
@@ -554,14 +588,14 @@ int qap_set_tile_rows(qap_handle h, int32_t algo, int32_t rows) {
     if (!h || algo < 0 || algo > 2) return QAP_E_INVALID;
     if (rows == 0) {
         h->rows_choice[algo] = h->rows_default[algo];
-        if (algo < 2) h->auto_rows[algo] = 1;
+        h->auto_rows[algo] = 1;
         return QAP_OK;
     }
     const int ri = rows_index(rows);
     if (ri < 0) return QAP_E_INVALID;
     if (!algo_fits(h, algo, ri)) return QAP_E_UNSUPPORTED;
     h->rows_choice[algo] = ri;
-    if (algo < 2) h->auto_rows[algo] = 0;
+    h->auto_rows[algo] = 0;
     return QAP_OK;
 }
 
@@ -605,8 +639,8 @@ int qap_tune_tile_rows(qap_handle h, int32_t algo, int32_t k, int32_t iters, flo
     if (e == hipSuccess) e = hipEventCreate(&e1);
     if (e == hipSuccess) e = hipMemcpyAsync(ds.p, hp.data(), hp.size() * 4, hipMemcpyHostToDevice, c.st);
     const int saved = h->rows_choice[algo];
-    const int saved_auto = algo < 2 ? h->auto_rows[algo] : 0;
-    if (algo < 2) h->auto_rows[algo] = 0;   // time exactly the shape set below
+    const int saved_auto = h->auto_rows[algo];
+    h->auto_rows[algo] = 0;   // time exactly the shape set below
     int best = -1, rc = QAP_OK;
     float best_ms = 0.0f;
     for (int ri = 0; ri <= kStream && e == hipSuccess && rc == QAP_OK; ++ri) {
@@ -651,7 +685,7 @@ int qap_tune_tile_rows(qap_handle h, int32_t algo, int32_t k, int32_t iters, flo
         }
     }
     h->rows_choice[algo] = best >= 0 ? best : saved;
-    if (algo < 2 && best < 0) h->auto_rows[algo] = saved_auto;
+    if (best < 0) h->auto_rows[algo] = saved_auto;
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
     if (e != hipSuccess) return dev_err(e);
@@ -756,7 +790,11 @@ int qap_tabu_noalloc_async(qap_handle h, int32_t *d_perms, int32_t k, int32_t it
     StreamScratch pre{reinterpret_cast<int4 *>(base + table_bytes)};
     const hipStream_t st = (hipStream_t)stream;
     TableArgs ta{h->d_mats, d_perms, nullptr, d_table, h->n, h->m, k, h->sym};
-    hipError_t e = launch_table(ta, st);
+    hipError_t e = hipSuccess;
+    if (use_block(h, 0, lo, hi))
+        d_table = nullptr;   // the block form makes its first neighbourhood itself
+    else
+        e = launch_table(ta, st);
     if (e == hipSuccess)
         e = launch_searches(h, 0, d_perms, d_table, k, iters, lo, hi, seed, start_base, d_best, d_done, st, false,
                             nullptr, 0, 0, ri, &pre);
@@ -868,7 +906,7 @@ int batch_create_impl(const qap_handle *hs, int32_t m, const int32_t *k_per, int
     std::vector<Item> items;
     std::vector<WideTable> wide_tables;
     long long perm_off = 0, out_off = 0, table_off = 0, tile_off = 0, freq_off = 0, uloc_off = 0;
-    size_t gsmem[BV_COUNT] = {}, tsmem = 0, fsmem = 0;
+    size_t gsmem[GV_COUNT] = {}, tsmem = 0, fsmem = 0;
     for (int i = 0; i < m; ++i) {
         qap_ctx *h = hs[i];
         if (!h || k_per[i] < 0 || !tenure_args_ok(iters, lo_per[i], hi_per[i])) return QAP_E_INVALID;
@@ -891,12 +929,18 @@ int batch_create_impl(const qap_handle *hs, int32_t m, const int32_t *k_per, int
         const size_t sm = streamed ? stream_smem_bytes(h->n, h->sym)
                                    : search_smem_bytes(h->n, rows, freq ? BATCH_LANES : batch_variant_lanes(var),
                                                        h->sym);
+        const bool block = !freq && !(rows_per && rows_per[i] != 0) && use_block(h, 2, lo_per[i], hi_per[i]);
         if (freq)
             fsmem = std::max(fsmem, sm);
+        else if (block)
+            gsmem[block_variant(h->n, h->sym)] =
+                std::max(gsmem[block_variant(h->n, h->sym)], block_smem_bytes(h->n, h->sym, hi_per[i], true));
         else
             gsmem[var] = std::max(gsmem[var], sm);
         const bool wide = h->n > WIDE_N;
-        if (wide) {
+        if (block) {
+            // makes its first neighbourhood itself
+        } else if (wide) {
             if (k_per[i] > 0)
                 wide_tables.push_back(WideTable{h->d_mats, h->n, h->m, k_per[i], h->sym, perm_off, table_off});
         } else {
@@ -913,7 +957,8 @@ int batch_create_impl(const qap_handle *hs, int32_t m, const int32_t *k_per, int
             it.ninterior = ts.ninterior;
             it.rows = streamed ? STREAM_ROWS : kRowsChoices[ri];
             it.stream = streamed ? 1 : 0;
-            if (streamed) {
+            it.blk = block ? h->blk : 0;
+            if (streamed && !block) {
                 it.tile_off = tile_off;
                 tile_off += stream_tile_int4(ts.ntiles);
             }
@@ -940,7 +985,7 @@ int batch_create_impl(const qap_handle *hs, int32_t m, const int32_t *k_per, int
             items.push_back(it);
             perm_off += h->n;
             out_off += 1;
-            table_off += h->m;
+            if (!block) table_off += h->m;
         }
     }
     // grouped by kernel variant; longest first inside a group (the hardware starts blocks
@@ -966,11 +1011,13 @@ int batch_create_impl(const qap_handle *hs, int32_t m, const int32_t *k_per, int
         if (v < 0) continue;   // (not reached: batch_fits and batch_freq_fits turn such shapes away)
         b->group_begin[v] = i;
         ++b->group_count[v];
+        ++b->tile_count[tile_variant(items[i])];
+        b->narrow += v < BV_WIDE;
     }
     int ngroups = 0;
-    long long work[BV_COUNT] = {};   // a group's work estimate: the sum of n^2 over its searches
-    int order[BV_COUNT];
-    for (int v = 0; v < BV_COUNT; ++v) {
+    long long work[GV_COUNT] = {};   // a group's work estimate: the sum of n^2 over its searches
+    int order[GV_COUNT];
+    for (int v = 0; v < GV_COUNT; ++v) {
         b->group_smem[v] = gsmem[v];
         ngroups += b->group_count[v] > 0;
         for (int i = 0; i < b->group_count[v]; ++i) {
@@ -979,11 +1026,11 @@ int batch_create_impl(const qap_handle *hs, int32_t m, const int32_t *k_per, int
         }
         order[v] = v;
     }
-    std::stable_sort(order, order + BV_COUNT, [&](int x, int y) { return work[x] > work[y]; });
+    std::stable_sort(order, order + GV_COUNT, [&](int x, int y) { return work[x] > work[y]; });
     if (!freq && ngroups > 0) {
         b->nlanes = std::min(ngroups, side_lanes());
-        long long load[BV_COUNT] = {};
-        int lane_of[BV_COUNT], per_lane[BV_COUNT] = {};
+        long long load[GV_COUNT] = {};
+        int lane_of[GV_COUNT], per_lane[GV_COUNT] = {};
         for (int g = 0; g < ngroups; ++g) {   // largest first, each to the least loaded lane
             int l = 0;
             for (int x = 1; x < b->nlanes; ++x)
@@ -998,21 +1045,21 @@ int batch_create_impl(const qap_handle *hs, int32_t m, const int32_t *k_per, int
         // launched first they take units before the smaller blocks of the other lanes
         // fill them (uneven batch: 138.4 -> 134.4 ms per step).
         auto longest = [&](int v) { return (long long)items[b->group_begin[v]].n; };   // items sorted by n
-        long long lane_max[BV_COUNT] = {};
+        long long lane_max[GV_COUNT] = {};
         for (int g = 0; g < ngroups; ++g) {
             const int l = lane_of[order[g]];
             lane_max[l] = std::max(lane_max[l], longest(order[g]));
         }
-        int lane_rank[BV_COUNT];
+        int lane_rank[GV_COUNT];
         for (int l = 0; l < b->nlanes; ++l) lane_rank[l] = l;
         std::stable_sort(lane_rank, lane_rank + b->nlanes, [&](int x, int y) { return lane_max[x] > lane_max[y]; });
-        int slot_of[BV_COUNT];
+        int slot_of[GV_COUNT];
         for (int i = 0; i < b->nlanes; ++i) slot_of[lane_rank[i]] = i;
         for (int i = 0; i < b->nlanes; ++i) b->lane_begin[i + 1] = b->lane_begin[i] + per_lane[lane_rank[i]];
-        int in_lane[BV_COUNT];
+        int in_lane[GV_COUNT];
         for (int g = 0; g < ngroups; ++g) in_lane[g] = order[g];
         std::stable_sort(in_lane, in_lane + ngroups, [&](int x, int y) { return longest(x) > longest(y); });
-        int fill[BV_COUNT] = {};
+        int fill[GV_COUNT] = {};
         for (int g = 0; g < ngroups; ++g) {
             const int v = in_lane[g], i = slot_of[lane_of[v]];
             b->lane_groups[b->lane_begin[i] + fill[i]++] = v;
@@ -1083,18 +1130,18 @@ extern "C" int qap_batch_groups(qap_batch_handle b, int32_t *count_out) {
         if (count_out) {
             for (int v = 0; v < BV_COUNT; ++v) count_out[v] = 0;
             for (int v = 0; v < BV_COUNT; ++v) {
-                if (!b->group_count[v]) continue;
+                if (!b->tile_count[v]) continue;
                 const int rows = v == BV_R4 || v == BV_R4_256 || v == BV_R4_768 ? 4 : (v == BV_R8 ? 8 : 2);
                 count_out[v == BV_STREAM ? BV_STREAM : (rows == 2 ? BV_R2 : (rows == 4 ? BV_R4 : BV_R8))] +=
-                    b->group_count[v];
+                    b->tile_count[v];
             }
         }
         return b->count > 0 ? 1 : 0;
     }
     int groups = 0;
     for (int v = 0; v < BV_COUNT; ++v) {
-        if (count_out) count_out[v] = b->group_count[v];
-        groups += b->group_count[v] > 0;
+        if (count_out) count_out[v] = b->tile_count[v];
+        groups += b->tile_count[v] > 0;
     }
     return groups;
 }
@@ -1103,9 +1150,7 @@ extern "C" int qap_batch_tables_async(qap_batch_handle b, const int32_t *d_perms
     if (!b || (b->count > 0 && !d_perms)) return QAP_E_INVALID;
     if (b->count == 0) return QAP_OK;
     const hipStream_t st = (hipStream_t)stream;
-    // the searches above WIDE_N come last (their variant is the last one)
-    const int narrow = b->count - (b->freq_mode ? 0 : b->group_count[BV_WIDE]);
-    BatchArgs a{b->d_items, narrow, const_cast<int32_t *>(d_perms), nullptr, nullptr, b->d_table, b->d_tile_work};
+    BatchArgs a{b->d_items, b->freq_mode ? b->count : b->narrow, const_cast<int32_t *>(d_perms), nullptr, nullptr, b->d_table, b->d_tile_work};
     hipError_t e = launch_table_batch(a, b->table_smem, st);
     for (size_t i = 0; i < b->wide_tables.size() && e == hipSuccess; ++i) {
         const WideTable &w = b->wide_tables[i];
@@ -1133,7 +1178,11 @@ extern "C" int qap_batch_search_async(qap_batch_handle b, int32_t *d_perms, int6
             const int v = b->lane_groups[g];
             BatchArgs a{b->d_items + b->group_begin[v], b->group_count[v], d_perms, d_best, d_done, b->d_table,
                         b->d_tile_work};
-            e = launch_batch_group(v, a, b->group_smem[v], ls);
+            if (v >= BV_COUNT)
+                e = launch_block(true, 32 * ((v - BV_COUNT) / 2 + 1), (v - BV_COUNT) & 1, b->group_smem[v], nullptr, &a,
+                                 a.count, ls);
+            else
+                e = launch_batch_group(v, a, b->group_smem[v], ls);
         }
         if (fork && e == hipSuccess) e = hipEventRecord(b->ev_join[l], ls);
     }
@@ -1156,7 +1205,7 @@ extern "C" int qap_batch_destroy(qap_batch_handle b) {
     if (b->d_tile_work) (void)hipFree(b->d_tile_work);
     if (b->d_freq) (void)hipFree(b->d_freq);
     if (b->d_uloc) (void)hipFree(b->d_uloc);
-    for (int v = 0; v < BV_COUNT; ++v) {
+    for (int v = 0; v < GV_COUNT; ++v) {
         if (b->side[v]) (void)hipStreamDestroy(b->side[v]);
         if (b->ev_join[v]) (void)hipEventDestroy(b->ev_join[v]);
     }

@@ -19,8 +19,10 @@ extern const int kRowsChoices[kShapes];
 std::vector<int32_t> enumerate_tiles(int n, int rows, int *ninterior);
 
 // Range-check F and D (entries in [0, 255]) and pack [F | F^T | D | D^T] as u8 rows of
-// row_stride(n) bytes; *sym = 1 when F and D are both symmetric.  QAP_OK or QAP_E_RANGE.
-int pack_instance(const int32_t *F, const int32_t *D, int n, std::vector<uint8_t> &pack, int *sym);
+// row_stride(n) bytes; *sym = 1 when F and D are both symmetric; *blk (see block_ok): 1 when
+// the entries of F span at most 127 and no more than those of D, 2 the other way round, 0
+// when both span more.  QAP_OK or QAP_E_RANGE.
+int pack_instance(const int32_t *F, const int32_t *D, int n, std::vector<uint8_t> &pack, int *sym, int *blk);
 
 // Map a HIP status to a QAP code (QAP_VERBOSE in the environment also reports it).
 int dev_err_at(hipError_t e, const char *where);

@@ -151,6 +151,7 @@ struct SearchArgs {
     int32_t *uloc;           // attr 2: [k][n][n] per search, until when a unit may not return to a location
     long long *trace;        // with freq: [k][trace_cap][4] (r, s, delta, cost after) per move, or null
     int trace_cap;
+    int blk;                 // block form: the matrix whose entries span more, 1 D, 2 F; 0 not served
 };
 
 // With QAP_VERBOSE set in the environment, report a failed HIP call on stderr.
@@ -227,6 +228,7 @@ struct Item {
     // with freq: the first trace_cap moves as (r, s, delta, cost after), or null
     long long *trace;
     int trace_cap;
+    int blk;                  // block form: the matrix whose entries span more, 1 D, 2 F; 0 not served
 };
 
 // The batched launch: one block per item of `items`; per-start buffers are shared by
@@ -306,6 +308,19 @@ hipError_t launch_resume(const Item *d_items, int count, size_t smem, hipStream_
 hipError_t launch_resume_freq(const Item *d_items, int count, size_t smem, hipStream_t st);
 // The same for items above WIDE_N (the wide streamed form).
 hipError_t launch_resume_wide(const Item *d_items, int count, size_t smem, hipStream_t st);
+// Block form (qap_block.hip): the neighbourhood as 32 x 32 blocks in matrix-core
+// accumulators.  Serves plain tabu searches and 2opt of n up to 32 BLOCK_MAX_NB whose LDS
+// fits, where the entries of F or of D span at most 127 (blk, from the instance; the
+// update's limbs hold no more), and for tabu hi - lo < 64 (the expiring moves of an
+// iteration are found by the lanes of one wave) and hi <= BLOCK_MAX_TENURE (its ring).
+constexpr int BLOCK_MAX_NB = 6;
+constexpr int BLOCK_MAX_TENURE = 1000;
+int block_nb(int n);
+size_t block_smem_bytes(int n, int sym, int hi, bool tabu);
+int block_ok(int n, int sym, int blk, bool tabu, int lo, int hi, size_t max_smem);
+// One search per block: of one instance (a), or items of one (block_nb, sym) of a batch (b).
+hipError_t launch_block(bool tabu, int n, int sym, size_t smem, const SearchArgs *a, const BatchArgs *b, int grid,
+                        hipStream_t st);
 // Lanes of a search workgroup for a tile shape, or 0 if the shape cannot serve n.
 int search_lanes(int n, int rows, int ntiles, int sym);
 

@@ -572,7 +572,8 @@ int qap_server_submit_matrices(qap_server_handle s, const int32_t *F, const int3
     if (!check_perms(start, 1, n)) return QAP_E_NOT_PERM;
     Request *r = new (std::nothrow) Request;
     if (!r) return QAP_E_NOMEM;
-    int rc = pack_instance(F, D, n, r->mats, &r->sym);
+    int blk = 0;
+    int rc = pack_instance(F, D, n, r->mats, &r->sym, &blk);
     std::lock_guard<std::mutex> lk(s->mu);
     if (rc == QAP_OK) rc = plan_request(s, r, n);
     if (rc == QAP_OK) rc = enqueue(s, r, n, start, iters, lo, hi, seed, ticket_out);

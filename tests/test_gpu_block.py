@@ -1,0 +1,180 @@
+"""GPU parity of the block form of the searches (the neighbourhood as 32 x 32 blocks in
+matrix-core accumulators) with the CPU oracle, bit for bit: the sizes where a block, a
+row step or a workgroup shape begins or ends, entries that fill the update's limbs or no
+longer fit them (those instances take the tile kernels), and tenures at the limits of its
+expiry lists.  All results are integers; equality is exact."""
+import os
+import sys
+from concurrent.futures import ThreadPoolExecutor
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2307_11248_amd import qap
+from paper_2307_11248_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+WORKERS = max(1, min(16, os.cpu_count() or 1))
+
+
+def note(msg):
+    sys.__stderr__.write("[gpu-case] %s\n" % msg)
+    sys.__stderr__.flush()
+
+
+def pmap(f, items):
+    with ThreadPoolExecutor(WORKERS) as ex:
+        return list(ex.map(f, items))
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    torch.cuda.init()
+    yield
+
+
+def check_tabu(F, D, perms, iters, lo, hi, seed, got):
+    res = pmap(lambda j: oracle.tabu(F, D, perms[j], iters, lo, hi, seed, j), range(len(perms)))
+    for j, r in enumerate(res):
+        assert (got[0][j] == r[0]).all() and got[1][j] == r[1] and got[2][j] == r[2], (j, got[1][j], r[1], got[2][j], r[2])
+
+
+def instance(n, sym, diag, hiF, hiD):
+    rng = np.random.default_rng([n, sym, diag, hiF, hiD])
+    F, _ = W.random_instance(rng, n, 0, hiF, symmetric=sym, diag=diag)
+    D, _ = W.random_instance(rng, n, 0, hiD, symmetric=sym, diag=diag)
+    return F, D, rng
+
+
+# sizes at the edges of blocks (32), row steps (16 and 64 bytes), workgroup shapes (blocks
+# per wave change above 128 and 160) and LDS (general instances above about 180 fall back)
+SIZES = [2, 3, 16, 31, 32, 33, 48, 63, 64, 65, 95, 96, 97, 127, 128, 129, 144, 159, 160, 161, 176, 192]
+
+
+@pytest.mark.parametrize("n", SIZES)
+@pytest.mark.parametrize("sym", [False, True])
+def test_block_sizes(n, sym):
+    note("block n=%d sym=%d" % (n, sym))
+    F, D, rng = instance(n, sym, n % 3 == 0, 99, 255)
+    perms = W.starts(rng, n, 3)
+    lo, hi = W.tabu_tenure_range(n)
+    iters = 3 * n + 40   # past the first expiries
+    with qap.Handle(F, D) as h:
+        check_tabu(F, D, perms, iters, lo, hi, 5, h.tabu(perms, iters, lo, hi, 5))
+        p, c, st = h.two_opt(perms)
+    for j, r in enumerate(pmap(lambda q: oracle.two_opt(F, D, q), list(perms))):
+        assert (p[j] == r[0]).all() and c[j] == r[1] and st[j] == r[2], j
+
+
+# spans at and past what the limbs hold (one of the two at most 127), the wider matrix in
+# either place, entries with an offset, and entries that tie everywhere
+@pytest.mark.parametrize("hiF,hiD,base", [(255, 127, 0), (127, 255, 0), (128, 255, 0), (255, 255, 0), (127, 127, 128),
+                                          (1, 1, 0), (1, 255, 0), (0, 9, 0)])
+@pytest.mark.parametrize("n,sym", [(37, False), (70, True)])
+def test_block_entry_spans(hiF, hiD, base, n, sym):
+    note("block spans F %d D %d + %d n=%d sym=%d" % (hiF, hiD, base, n, sym))
+    F, D, rng = instance(n, sym, True, hiF, hiD)
+    F, D = F + base, D + base
+    perms = W.starts(rng, n, 3)
+    lo, hi = W.tabu_tenure_range(n)
+    with qap.Handle(F, D) as h:
+        check_tabu(F, D, perms, 250, lo, hi, 9, h.tabu(perms, 250, lo, hi, 9))
+
+
+# tenures: none, shorter than the two iterations a move needs to be tabu at all, so short
+# that pairs are made again while listed, the widest range of one wave's expiry list (64
+# values) and one more (tile kernels), the longest of its ring and one more, and a small
+# instance on which every move is tabu and the search stops
+@pytest.mark.parametrize("n,lo,hi", [(20, 0, 0), (20, 0, 2), (33, 1, 5), (33, 2, 2), (50, 0, 63), (50, 0, 64),
+                                     (50, 990, 1000), (50, 1001, 1001), (4, 5, 9), (6, 40, 60), (40, 4, 13)])
+def test_block_tenures(n, lo, hi):
+    note("block tenures n=%d lo=%d hi=%d" % (n, lo, hi))
+    F, D, rng = instance(n, False, False, 9, 9)   # many ties and aspirations
+    perms = W.starts(rng, n, 4)
+    with qap.Handle(F, D) as h:
+        check_tabu(F, D, perms, 1500, lo, hi, 3, h.tabu(perms, 1500, lo, hi, 3))
+
+
+def test_block_entry_points_agree():
+    """One launch, one launch per start, from a given table, without allocation, in a batch,
+    in a captured graph replayed between other work, and with a tile shape set."""
+    import torch
+    n, k, iters = 75, 5, 400
+    note("block entry points n=%d" % n)
+    F, D, rng = instance(n, False, False, 99, 99)
+    perms = W.starts(rng, n, k)
+    perms[3, 0] = perms[3, 1]   # not a permutation: left as it is, marked
+    lo, hi = W.tabu_tenure_range(n)
+    starts = torch.from_numpy(perms).cuda()
+    table = torch.empty((k, n * (n - 1) // 2), dtype=torch.int32, device="cuda")
+    with qap.Handle(F, D) as h, qap.Batch([h], [k], iters, [lo], [hi], [7]) as plan:
+        stream = torch.cuda.Stream()
+        p, c, d = torch.empty_like(starts), torch.empty(k, dtype=torch.int64, device="cuda"), \
+            torch.empty(k, dtype=torch.int32, device="cuda")
+        calls = {
+            "launch": lambda: h.tabu_async(p, iters, lo, hi, 7, c, d, stream=stream),
+            "plain": lambda: h.tabu_async(p, iters, lo, hi, 7, c, d, stream=stream, plain=True),
+            "noalloc": lambda: h.tabu_noalloc_async(p, iters, lo, hi, 7, c, d, stream=stream),
+            "table": lambda: (h.delta_table_async(p, table, stream=stream),
+                              h.tabu_with_table_async(p, table, iters, lo, hi, 7, c, d, stream=stream)),
+            "batch": lambda: plan.run_async(p, c, d, stream=stream),
+        }
+        out = {}
+        for name, call in calls.items():
+            with torch.cuda.stream(stream):
+                p.copy_(starts)
+                c.fill_(0)
+                call()
+            torch.cuda.synchronize()
+            out[name] = (p.cpu().numpy(), c.cpu().numpy(), d.cpu().numpy())
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=stream):
+            p.copy_(starts)
+            calls["launch"]()
+        for i in range(3):
+            p.fill_(0)
+            h.cost_async(starts, c)
+            torch.cuda.synchronize()
+            g.replay()
+            torch.cuda.synchronize()
+            out["graph %d" % i] = (p.cpu().numpy(), c.cpu().numpy(), d.cpu().numpy())
+        h.set_tile_rows("tabu", 4)
+        with torch.cuda.stream(stream):
+            p.copy_(starts)
+            calls["launch"]()
+        torch.cuda.synchronize()
+        out["tiles"] = (p.cpu().numpy(), c.cpu().numpy(), d.cpu().numpy())
+    good = [0, 1, 2, 4]
+    ref = pmap(lambda j: oracle.tabu(F, D, perms[j], iters, lo, hi, 7, j), good)
+    for name, (gp, gc, gd) in out.items():
+        for j, r in zip(good, ref):
+            assert (gp[j] == r[0]).all() and gc[j] == r[1] and gd[j] == r[2], (name, j)
+        assert (gp[3] == perms[3]).all() and gc[3] == np.iinfo(np.int64).min and gd[3] == qap.QAP_E_NOT_PERM, name
+
+
+def test_block_batch_of_every_size():
+    """A batch whose searches need every kernel of the block form and the tile kernels."""
+    sizes = [8, 32, 40, 64, 90, 96, 100, 128, 150, 160, 170, 50, 200]
+    k, iters = 2, 300
+    note("block batch sizes=%s" % sizes)
+    insts, lohi, seeds = [], [], []
+    for t, n in enumerate(sizes * 2):
+        F, D, rng = instance(n, t >= len(sizes), False, 255 if n == 50 else 99, 255)
+        insts.append((F, D, W.starts(rng, n, k)))
+        lohi.append(W.tabu_tenure_range(n))
+        seeds.append(100 + t)
+    hs = [qap.Handle(F, D) for F, D, _ in insts]
+    cat = np.concatenate([P.reshape(-1) for _, _, P in insts]).astype(np.int32)
+    p, c, d = qap.tabu_batch(hs, cat, [k] * len(hs), iters, [a for a, _ in lohi], [b for _, b in lohi], seeds)
+    off = 0
+    for t, (F, D, P) in enumerate(insts):
+        n = len(F)
+        got = (p[off:off + k * n].reshape(k, n), c[t * k:t * k + k], d[t * k:t * k + k])
+        check_tabu(F, D, P, iters, lohi[t][0], lohi[t][1], seeds[t], got)
+        off += k * n
+    for h in hs:
+        h.close()
