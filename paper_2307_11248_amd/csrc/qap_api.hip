@@ -284,7 +284,7 @@ hipError_t launch_searches(qap_ctx *h, int algo, int32_t *d_perms, const int32_t
         const size_t smem = block_smem_bytes(h->n, h->sym, hi, algo == 0);
         for (int j = 0; j < (plain ? k : 1) && e == hipSuccess; ++j) {
             a.job0 = j;
-            e = launch_block(algo == 0, h->n, h->sym, smem, &a, nullptr, plain ? 1 : k, st);
+            e = launch_block(algo == 0, block_form(h->n, h->sym), !plain && k > h->cus, smem, &a, nullptr, plain ? 1 : k, st);
         }
         return e;
     }
@@ -421,8 +421,8 @@ struct WideTable {
     long long perm_off, table_off;
 };
 
-// Kernel variants of a batch: the tile shapes, then the block form by (block_nb, sym).
-constexpr int GV_COUNT = BV_COUNT + 2 * BLOCK_MAX_NB;
+// Kernel variants of a batch: the tile shapes, then the block form's kernels.
+constexpr int GV_COUNT = BV_COUNT + BLOCK_FORMS;
 
 struct qap_batch {
     int count = 0;                  // searches (items)
@@ -435,10 +435,11 @@ struct qap_batch {
     // (offsets into the run's starts and the plan's tables); the matrix-core table kernel
     // takes every other item
     std::vector<WideTable> wide_tables;
-    // items are grouped by kernel variant: the tile shapes, then the block form's kernels
-    // (one per (block_nb, sym)); one launch per non-empty group
+    // items are grouped by kernel variant: the tile shapes, then the block form's kernels;
+    // one launch per non-empty group
     int group_begin[GV_COUNT] = {}, group_count[GV_COUNT] = {};
     size_t group_smem[GV_COUNT] = {};
+    bool busy = false;              // more searches than compute units
     int narrow = 0;                 // items of the tile shapes up to WIDE_N (they come first)
     int tile_count[BV_COUNT] = {};  // searches per tile shape, reported by qap_batch_groups
     // The groups run on `nlanes` side streams forked from the caller's stream, the groups
@@ -463,7 +464,7 @@ struct qap_batch {
 namespace {
 
 int tile_variant(const Item &it) { return batch_variant(it.n, it.rows, it.stream != 0, it.ntiles, it.sym); }
-int block_variant(int n, int sym) { return BV_COUNT + 2 * (block_nb(n) - 1) + sym; }
+int block_variant(int n, int sym) { return BV_COUNT + block_form(n, sym); }
 int item_variant(const Item &it) { return it.blk ? block_variant(it.n, it.sym) : tile_variant(it); }
 
 // ---- fixed scratch of qap_tabu_noalloc_async: one array per GPU, held until the process
@@ -998,6 +999,7 @@ int batch_create_impl(const qap_handle *hs, int32_t m, const int32_t *k_per, int
     qap_batch *b = new (std::nothrow) qap_batch;
     if (!b) return QAP_E_NOMEM;
     b->count = (int)items.size();
+    b->busy = m > 0 && b->count > hs[0]->cus;
     b->perm_ints = perm_off;
     b->table_ints = table_off;
     b->tile_int4 = tile_off;
@@ -1179,8 +1181,7 @@ extern "C" int qap_batch_search_async(qap_batch_handle b, int32_t *d_perms, int6
             BatchArgs a{b->d_items + b->group_begin[v], b->group_count[v], d_perms, d_best, d_done, b->d_table,
                         b->d_tile_work};
             if (v >= BV_COUNT)
-                e = launch_block(true, 32 * ((v - BV_COUNT) / 2 + 1), (v - BV_COUNT) & 1, b->group_smem[v], nullptr, &a,
-                                 a.count, ls);
+                e = launch_block(true, v - BV_COUNT, b->busy, b->group_smem[v], nullptr, &a, a.count, ls);
             else
                 e = launch_batch_group(v, a, b->group_smem[v], ls);
         }

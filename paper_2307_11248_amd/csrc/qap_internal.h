@@ -194,6 +194,7 @@ struct Item {
     SearchState *st;          // null: run from the start to `iters` in one go
     int32_t *st_perm, *st_bestp;
     int2 *st_du;              // chunked runs: (delta, tabu until) per packed pair index
+    int32_t *st_slots, *st_ring;   // chunked runs in block form: slots per packed pair index, ring of moves
     int n, m, sym, ntiles, ninterior, rows;
     int iters;                // tabu: last iteration of this run; 2opt: move cap (<= 0: none)
     int lo, hi;
@@ -309,17 +310,20 @@ hipError_t launch_resume_freq(const Item *d_items, int count, size_t smem, hipSt
 // The same for items above WIDE_N (the wide streamed form).
 hipError_t launch_resume_wide(const Item *d_items, int count, size_t smem, hipStream_t st);
 // Block form (qap_block.hip): the neighbourhood as 32 x 32 blocks in matrix-core
-// accumulators.  Serves plain tabu searches and 2opt of n up to 32 BLOCK_MAX_NB whose LDS
-// fits, where the entries of F or of D span at most 127 (blk, from the instance; the
-// update's limbs hold no more), and for tabu hi - lo < 64 (the expiring moves of an
-// iteration are found by the lanes of one wave) and hi <= BLOCK_MAX_TENURE (its ring).
-constexpr int BLOCK_MAX_NB = 6;
+// accumulators.  Serves plain tabu searches and 2opt up to WIDE_N whose LDS fits, where the
+// entries of F or of D span at most 127 (blk, from the instance; the update's limbs hold no
+// more), and for tabu hi - lo < 64 (the expiring moves of an iteration are found by the
+// lanes of one wave) and hi <= BLOCK_MAX_TENURE (its ring).
 constexpr int BLOCK_MAX_TENURE = 1000;
-int block_nb(int n);
+// Its kernels: one per (ceil(n / 32), sym).
+constexpr int BLOCK_FORMS = 16;
+int block_form(int n, int sym);
 size_t block_smem_bytes(int n, int sym, int hi, bool tabu);
+size_t block_ring_bytes(int hi);
 int block_ok(int n, int sym, int blk, bool tabu, int lo, int hi, size_t max_smem);
-// One search per block: of one instance (a), or items of one (block_nb, sym) of a batch (b).
-hipError_t launch_block(bool tabu, int n, int sym, size_t smem, const SearchArgs *a, const BatchArgs *b, int grid,
+// One search per block: of one instance (a), or items of one form of a batch (b); busy: the
+// searches in flight outnumber the compute units.
+hipError_t launch_block(bool tabu, int form, bool busy, size_t smem, const SearchArgs *a, const BatchArgs *b, int grid,
                         hipStream_t st);
 // Lanes of a search workgroup for a tile shape, or 0 if the shape cannot serve n.
 int search_lanes(int n, int rows, int ntiles, int sym);

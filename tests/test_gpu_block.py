@@ -51,8 +51,10 @@ def instance(n, sym, diag, hiF, hiD):
 
 
 # sizes at the edges of blocks (32), row steps (16 and 64 bytes), workgroup shapes (blocks
-# per wave change above 128 and 160) and LDS (general instances above about 180 fall back)
-SIZES = [2, 3, 16, 31, 32, 33, 48, 63, 64, 65, 95, 96, 97, 127, 128, 129, 144, 159, 160, 161, 176, 192]
+# per wave change above 128, 160, 192 and 224) and LDS layouts (general instances above 176
+# read D from global memory; above 224 the rows are exactly 256 bytes)
+SIZES = [2, 3, 16, 31, 32, 33, 48, 63, 64, 65, 95, 96, 97, 127, 128, 129, 144, 159, 160, 161, 176, 177, 191, 192, 193,
+         208, 223, 224, 225, 240, 241, 255, 256]
 
 
 @pytest.mark.parametrize("n", SIZES)
@@ -158,7 +160,7 @@ def test_block_entry_points_agree():
 
 def test_block_batch_of_every_size():
     """A batch whose searches need every kernel of the block form and the tile kernels."""
-    sizes = [8, 32, 40, 64, 90, 96, 100, 128, 150, 160, 170, 50, 200]
+    sizes = [8, 32, 40, 64, 90, 96, 100, 128, 150, 160, 170, 50, 180, 200, 240, 260]
     k, iters = 2, 300
     note("block batch sizes=%s" % sizes)
     insts, lohi, seeds = [], [], []
