@@ -125,11 +125,12 @@ struct qap_ctx {
 };
 
 namespace qaph {
-bool handle_view(const qap_ctx *h, const uint8_t **mats, int *n, int *sym, int *device) {
+bool handle_view(const qap_ctx *h, const uint8_t **mats, int *n, int *sym, int *blk, int *device) {
     if (!h) return false;
     *mats = h->d_mats;
     *n = h->n;
     *sym = h->sym;
+    *blk = h->blk;
     *device = h->device;
     return true;
 }

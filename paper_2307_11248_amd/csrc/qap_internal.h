@@ -325,6 +325,9 @@ int block_ok(int n, int sym, int blk, bool tabu, int lo, int hi, size_t max_smem
 // searches in flight outnumber the compute units.
 hipError_t launch_block(bool tabu, int form, bool busy, size_t smem, const SearchArgs *a, const BatchArgs *b, int grid,
                         hipStream_t st);
+// One chunk of resumable searches (st != null) of any form: their slots are kept between
+// chunks in st_slots (m int32), their ring of moves in st_ring (block_ring_bytes).
+hipError_t launch_resume_block(const Item *d_items, int count, size_t smem, hipStream_t st);
 // Lanes of a search workgroup for a tile shape, or 0 if the shape cannot serve n.
 int search_lanes(int n, int rows, int ntiles, int sym);
 

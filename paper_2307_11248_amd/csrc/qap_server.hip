@@ -38,6 +38,8 @@ namespace {
 constexpr size_t kAlign = 256;
 // Steps a queued request may be passed over by later ones before admission waits for it.
 constexpr int kMaxPassOvers = 8;
+// Kernels of a step: block form, other plain searches, frequency memory, above WIDE_N.
+constexpr int kGroups = 4;
 
 size_t up(size_t x) { return (x + kAlign - 1) & ~(kAlign - 1); }
 
@@ -118,6 +120,7 @@ struct Request {
     int64_t ticket = 0;
     int n = 0, m = 0, sym = 0, rows = 0, iters = 0, lo = 0, hi = 0;
     bool streamed = false;
+    int blk = 0;             // of pack_instance; 0 once the block form does not serve the request
     uint64_t seed = 0;
     bool freq = false;       // keeps the frequency memory (qap_server_submit_freq)
     int div = 0, attr = 0;
@@ -161,6 +164,8 @@ struct qap_server {
     size_t max_smem = 0;
     long long budget_ticks = 0;
     hipStream_t st = nullptr;
+    hipStream_t side[kGroups] = {};        // (0 unused) the other groups of a step
+    hipEvent_t ev_fork = nullptr, ev_join[kGroups] = {};
     uint8_t *pool = nullptr;
     size_t pool_bytes = 0;
     Arena arena;
@@ -240,7 +245,13 @@ Item make_item(qap_server *s, const Request *r) {
     Item it{};
     it.mats = r->ext_mats ? r->ext_mats : base + r->lay.mats;
     it.tiles = ts.d;
-    it.table = reinterpret_cast<const int32_t *>(base + r->lay.table);
+    it.blk = r->blk;
+    if (r->blk) {   // makes its first neighbourhood itself
+        it.st_slots = reinterpret_cast<int32_t *>(base + r->lay.table);
+        it.st_ring = reinterpret_cast<int32_t *>(base + (r->streamed ? r->lay.tile_work : r->lay.st_du));
+    } else {
+        it.table = reinterpret_cast<const int32_t *>(base + r->lay.table);
+    }
     it.perm_in = reinterpret_cast<const int32_t *>(base + r->lay.perm);
     it.perm_out = reinterpret_cast<int32_t *>(base + r->lay.perm);
     it.cost_out = s->d_cost + r->slot;
@@ -304,14 +315,18 @@ int enqueue(qap_server *s, Request *r, int32_t n, const int32_t *start, int32_t 
     return QAP_OK;
 }
 
-// Tile shape and layout of a request (s->mu held); QAP_OK or an error code.
-int plan_request(qap_server *s, Request *r, int n) {
+// Tile shape and layout of a request (s->mu held); QAP_OK or an error code.  A request the
+// block form serves keeps its slots and ring of moves in the regions of the tile shape's
+// table and saved state (no larger: a small n with a long tenure keeps the tile shape).
+int plan_request(qap_server *s, Request *r, int n, int lo, int hi) {
     int rc = QAP_OK;
     r->rows = server_rows(s, n, r->sym, &rc, r->freq);
     if (rc != QAP_OK) return rc;
     r->streamed = r->rows < 0;
     const Tiles &ts = s->tiles[n * 16 + (r->streamed ? STREAM_ROWS : r->rows)];
     r->lay = layout_for(n, r->streamed, ts.ntiles, r->ext_mats == nullptr, r->freq, r->attr);
+    const size_t saved = r->streamed ? (size_t)stream_tile_int4(ts.ntiles) * sizeof(int4) : up((size_t)n * (n - 1) / 2 * 8 + 16);
+    if (r->freq || !block_ok(n, r->sym, r->blk, true, lo, hi, s->max_smem) || block_ring_bytes(hi) > saved) r->blk = 0;
     if (up(r->lay.total) > s->pool_bytes) return QAP_E_NOMEM;   // could never be admitted
     return QAP_OK;
 }
@@ -320,8 +335,8 @@ int plan_request(qap_server *s, Request *r, int n) {
 // Called with s->step_mu held; takes s->mu only around the shared state.
 int step_locked(qap_server *s, int32_t *active_out, int32_t *pending_out) {
     hipError_t e = hipSuccess;
-    int nnew = 0, count = 0, ngroup[3] = {0, 0, 0};
-    size_t smem = 0, fsmem = 0, wsmem = 0, tsmem = 0;
+    int nnew = 0, count = 0, ngroup[kGroups] = {};
+    size_t gsmem[kGroups] = {}, tsmem = 0;
     std::vector<Request *> admitted, injected, fresh_wide;
     {
         std::lock_guard<std::mutex> lk(s->mu);
@@ -358,24 +373,23 @@ int step_locked(qap_server *s, int32_t *active_out, int32_t *pending_out) {
         }
         s->pending.swap(still);
         count = (int)s->active.size();
-        // one launch per kernel: plain searches up to WIDE_N, then those that keep the
-        // frequency memory, then those above WIDE_N (the wide streamed form)
-        auto group = [](const Request *r) { return r->n > WIDE_N ? 2 : (r->freq ? 1 : 0); };
+        // one launch per kernel: searches in block form, other plain searches up to WIDE_N,
+        // those that keep the frequency memory, those above WIDE_N (the wide streamed form)
+        auto group = [](const Request *r) { return r->n > WIDE_N ? 3 : (r->freq ? 2 : (r->blk ? 0 : 1)); };
         std::stable_sort(s->active.begin(), s->active.end(),
                          [&](const Request *x, const Request *y) { return group(x) < group(y); });
         for (int i = 0; i < count; ++i) {
             Request *r = s->active[i];
             s->h_items[i] = make_item(s, r);
             const int gr = group(r);
-            const bool wide = gr == 2;
             ++ngroup[gr];
-            size_t &sm = gr == 2 ? wsmem : (gr == 1 ? fsmem : smem);
-            sm = std::max(sm, r->streamed ? stream_smem_bytes(r->n, r->sym)
-                                          : search_smem_bytes(r->n, r->rows, BATCH_LANES, r->sym));
+            gsmem[gr] = std::max(gsmem[gr], gr == 0 ? block_smem_bytes(r->n, r->sym, r->hi, true)
+                                            : r->streamed ? stream_smem_bytes(r->n, r->sym)
+                                                          : search_smem_bytes(r->n, r->rows, BATCH_LANES, r->sym));
             if (r->fresh) {
-                if (wide) {
+                if (gr == 3) {
                     fresh_wide.push_back(r);
-                } else {
+                } else if (gr != 0) {
                     s->h_new[nnew++] = s->h_items[i];
                     tsmem = std::max(tsmem, table_smem_bytes(r->n));
                 }
@@ -422,10 +436,36 @@ int step_locked(qap_server *s, int32_t *active_out, int32_t *pending_out) {
             e = hipMemsetAsync(base + r->lay.perm, 0, (size_t)r->n * 4, s->st);
             if (e == hipSuccess) e = hipMemsetAsync(base + r->lay.st_perm, 0, (size_t)r->n * 4, s->st);
         }
-        if (e == hipSuccess) e = launch_resume(s->d_items, ngroup[0], smem, s->st);
-        if (e == hipSuccess) e = launch_resume_freq(s->d_items + ngroup[0], ngroup[1], fsmem, s->st);
-        if (e == hipSuccess)
-            e = launch_resume_wide(s->d_items + ngroup[0] + ngroup[1], ngroup[2], wsmem, s->st);
+        // the kernels run side by side: the first group in use on the server's stream, the
+        // others on streams forked from it and joined back (one after another, each would
+        // take a chunk's time of its own)
+        int off = 0, used = 0;
+        for (int g = 0; g < kGroups; ++g) used += ngroup[g] > 0;
+        if (used > 1 && e == hipSuccess) e = hipEventRecord(s->ev_fork, s->st);
+        bool first = true;
+        for (int g = 0; g < kGroups && e == hipSuccess; ++g) {
+            if (ngroup[g] == 0) continue;
+            hipStream_t st = s->st;
+            if (!first) {
+                st = s->side[g];
+                e = hipStreamWaitEvent(st, s->ev_fork, 0);
+                if (e != hipSuccess) break;
+            }
+            const Item *items = s->d_items + off;
+            e = g == 0   ? launch_resume_block(items, ngroup[g], gsmem[g], st)
+                : g == 1 ? launch_resume(items, ngroup[g], gsmem[g], st)
+                : g == 2 ? launch_resume_freq(items, ngroup[g], gsmem[g], st)
+                         : launch_resume_wide(items, ngroup[g], gsmem[g], st);
+            if (!first && e == hipSuccess) e = hipEventRecord(s->ev_join[g], st);
+            off += ngroup[g];
+            first = false;
+        }
+        first = true;
+        for (int g = 0; g < kGroups && e == hipSuccess; ++g) {
+            if (ngroup[g] == 0) continue;
+            if (!first) e = hipStreamWaitEvent(s->st, s->ev_join[g], 0);
+            first = false;
+        }
         if (e == hipSuccess)
             e = hipMemcpyAsync(s->h_state, s->d_state, (size_t)s->max_active * sizeof(SearchState),
                                hipMemcpyDeviceToHost, s->st);
@@ -532,6 +572,11 @@ int qap_server_create(int64_t pool_bytes, int32_t max_active, double chunk_ms, q
     s->max_smem = (size_t)smem;
     s->budget_ticks = chunk_ms > 0 ? std::max(1LL, (long long)(chunk_ms * khz)) : 0;
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&s->st, hipStreamNonBlocking);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&s->ev_fork, hipEventDisableTiming);
+    for (int g = 1; g < kGroups && e == hipSuccess; ++g) {
+        e = hipStreamCreateWithFlags(&s->side[g], hipStreamNonBlocking);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&s->ev_join[g], hipEventDisableTiming);
+    }
     if (e == hipSuccess) e = hipMalloc((void **)&s->pool, s->pool_bytes);
     if (e == hipSuccess) e = hipMalloc((void **)&s->d_state, (size_t)max_active * sizeof(SearchState));
     if (e == hipSuccess) e = hipMalloc((void **)&s->d_cost, (size_t)max_active * 8);
@@ -572,10 +617,9 @@ int qap_server_submit_matrices(qap_server_handle s, const int32_t *F, const int3
     if (!check_perms(start, 1, n)) return QAP_E_NOT_PERM;
     Request *r = new (std::nothrow) Request;
     if (!r) return QAP_E_NOMEM;
-    int blk = 0;
-    int rc = pack_instance(F, D, n, r->mats, &r->sym, &blk);
+    int rc = pack_instance(F, D, n, r->mats, &r->sym, &r->blk);
     std::lock_guard<std::mutex> lk(s->mu);
-    if (rc == QAP_OK) rc = plan_request(s, r, n);
+    if (rc == QAP_OK) rc = plan_request(s, r, n, lo, hi);
     if (rc == QAP_OK) rc = enqueue(s, r, n, start, iters, lo, hi, seed, ticket_out);
     if (rc != QAP_OK) delete r;
     return rc;
@@ -584,8 +628,8 @@ int qap_server_submit_matrices(qap_server_handle s, const int32_t *F, const int3
 int qap_server_submit(qap_server_handle s, qap_handle h, const int32_t *start, int32_t iters, int32_t lo,
                       int32_t hi, uint64_t seed, int64_t *ticket_out) {
     const uint8_t *mats = nullptr;
-    int n = 0, sym = 0, dev = 0;
-    if (!s || !start || !ticket_out || !handle_view(h, &mats, &n, &sym, &dev) || !tenure_args_ok(iters, lo, hi))
+    int n = 0, sym = 0, blk = 0, dev = 0;
+    if (!s || !start || !ticket_out || !handle_view(h, &mats, &n, &sym, &blk, &dev) || !tenure_args_ok(iters, lo, hi))
         return QAP_E_INVALID;
     if (dev != s->device) return QAP_E_INVALID;
     if (!check_perms(start, 1, n)) return QAP_E_NOT_PERM;
@@ -593,8 +637,9 @@ int qap_server_submit(qap_server_handle s, qap_handle h, const int32_t *start, i
     if (!r) return QAP_E_NOMEM;
     r->ext_mats = mats;
     r->sym = sym;
+    r->blk = blk;
     std::lock_guard<std::mutex> lk(s->mu);
-    int rc = plan_request(s, r, n);
+    int rc = plan_request(s, r, n, lo, hi);
     if (rc == QAP_OK) rc = enqueue(s, r, n, start, iters, lo, hi, seed, ticket_out);
     if (rc != QAP_OK) delete r;
     return rc;
@@ -603,8 +648,8 @@ int qap_server_submit(qap_server_handle s, qap_handle h, const int32_t *start, i
 int qap_server_submit_freq(qap_server_handle s, qap_handle h, const int32_t *start, int32_t iters, int32_t lo,
                            int32_t hi, uint64_t seed, int32_t div, int32_t attr, int64_t *ticket_out) {
     const uint8_t *mats = nullptr;
-    int n = 0, sym = 0, dev = 0;
-    if (!s || !start || !ticket_out || !handle_view(h, &mats, &n, &sym, &dev) || !tenure_args_ok(iters, lo, hi) ||
+    int n = 0, sym = 0, blk = 0, dev = 0;
+    if (!s || !start || !ticket_out || !handle_view(h, &mats, &n, &sym, &blk, &dev) || !tenure_args_ok(iters, lo, hi) ||
         div < 0 || attr < 0 || attr > 2)
         return QAP_E_INVALID;
     if (dev != s->device) return QAP_E_INVALID;
@@ -618,7 +663,7 @@ int qap_server_submit_freq(qap_server_handle s, qap_handle h, const int32_t *sta
     r->div = div;
     r->attr = attr;
     std::lock_guard<std::mutex> lk(s->mu);
-    int rc = plan_request(s, r, n);
+    int rc = plan_request(s, r, n, lo, hi);
     if (rc == QAP_OK) rc = enqueue(s, r, n, start, iters, lo, hi, seed, ticket_out);
     if (rc != QAP_OK) delete r;
     return rc;
@@ -804,6 +849,11 @@ int qap_server_destroy(qap_server_handle s) {
     if (s->h_state) (void)hipHostFree(s->h_state);
     if (s->h_cost) (void)hipHostFree(s->h_cost);
     if (s->h_moves) (void)hipHostFree(s->h_moves);
+    for (int g = 0; g < kGroups; ++g) {
+        if (s->side[g]) (void)hipStreamDestroy(s->side[g]);
+        if (s->ev_join[g]) (void)hipEventDestroy(s->ev_join[g]);
+    }
+    if (s->ev_fork) (void)hipEventDestroy(s->ev_fork);
     if (s->st) (void)hipStreamDestroy(s->st);
     delete s;
     return QAP_OK;

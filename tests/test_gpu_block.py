@@ -180,3 +180,41 @@ def test_block_batch_of_every_size():
         off += k * n
     for h in hs:
         h.close()
+
+
+def test_block_served_in_chunks():
+    """Requests of every workgroup shape of the block form, cut into many short chunks, beside
+    requests it does not serve (wide entries, a tenure longer than its ring, n above 256, the
+    frequency memory): every result equals the oracle's search run in one go."""
+    note("block served in chunks")
+    cases = [(20, 0, 99, None), (33, 1, 99, None), (64, 0, 99, (2, 9)), (97, 0, 99, None), (128, 1, 99, None),
+             (150, 0, 99, None), (176, 1, 99, None), (200, 0, 99, None), (250, 0, 99, None), (256, 1, 99, None),
+             (40, 0, 255, None), (45, 0, 99, (1002, 1005)), (3, 0, 99, (700, 705)), (260, 0, 99, None)]
+    iters = 700
+    srv = qap.Server(1 << 30, 64, 0.1)
+    want, tickets = [], []
+    for t, (n, sym, hi_entry, ten) in enumerate(cases):
+        F, D, rng = instance(n, sym, t % 2 == 0, hi_entry, 255)
+        p = W.starts(rng, n, 1)[0]
+        lo, hi = ten or W.tabu_tenure_range(n)
+        want.append((F, D, p, lo, hi))
+        tickets.append(srv.submit(F, D, p, iters, lo, hi, 40 + t))
+    F, D, rng = instance(60, 0, False, 99, 99)
+    pf = W.starts(rng, 60, 1)[0]
+    with qap.Handle(F, D) as h:
+        tf = srv.submit_freq(h, pf, iters, 54, 66, 5, 25, 1)
+        steps = 0
+        while True:
+            _, active, pending = srv.step()
+            steps += 1
+            if active == 0 and pending == 0:
+                break
+        assert steps > 3   # cut into chunks
+        fp, fc, ff = srv.poll_freq(tf)
+        r = oracle.tabu_freq(F, D, pf, iters, 54, 66, 5, 0, div=25, attr=1)
+        assert (fp == r[0]).all() and fc == r[1]
+    got = [srv.result(t) for t in tickets]
+    res = pmap(lambda a: oracle.tabu(a[1][0], a[1][1], a[1][2], iters, a[1][3], a[1][4], 40 + a[0], 0),
+               list(enumerate(want)))
+    for c, g, r in zip(cases, got, res):
+        assert (g[0] == r[0]).all() and g[1] == r[1] and g[2] == r[2], c
