@@ -431,6 +431,19 @@ int qap_server_destroy(qap_server_handle s);
  */
 int qap_set_tile_rows(qap_handle h, int32_t algo, int32_t rows);
 
+/*
+ * Plain tabu searches (no frequency memory) and 2opt up to n = 256 run in block form, not in
+ * tiles, unless a shape is set with qap_set_tile_rows (or passed to qap_batch_create): one
+ * workgroup per search that holds the neighbourhood as 32 x 32 blocks in matrix-core
+ * accumulators.  It takes instances in which the entries of F or of D span at most 127, and
+ * tenures with hi - lo < 64 and hi <= 1000; every other search runs in tiles.  Results do not
+ * depend on the form.  The functions here report the tile shape a launch would use (the
+ * searches of a batch in block form are counted by qap_batch_groups under theirs).
+ * qap_prefer_tile_rows is qap_set_tile_rows for the searches in tiles only: the block form
+ * keeps what it serves.  It is the state qap_tune_tile_rows leaves behind.
+ */
+int qap_prefer_tile_rows(qap_handle h, int32_t algo, int32_t rows);
+
 /* Tile rows currently used for algo, and the lanes per search in *lanes_out (may be
  * NULL); in the automatic mode, the shape of a launch of one start.  Same as
  * qap_launch_tile_rows(h, algo, 1, lanes_out). */

@@ -54,6 +54,11 @@ class TileCache:
             with open(self.path) as f:
                 self.entries = json.load(f)
 
+    @staticmethod
+    def _set(h, algo: str, rows: int):
+        # a tuned shape is for the searches that run in tiles (a set one would take them all)
+        getattr(h, "prefer_tile_rows", h.set_tile_rows)(algo, rows)
+
     def key(self, algo: str, n: int, sym: bool) -> str:
         return "%s|%s|%d|%s" % (self.prefix, algo, n, "sym" if sym else "asym")
 
@@ -63,7 +68,7 @@ class TileCache:
         rows = self.entries.get(k, {}).get("rows")
         if rows is not None:
             try:
-                h.set_tile_rows(algo, rows)
+                self._set(h, algo, rows)
                 return rows
             except qap.QapError:
                 pass                      # the cached shape no longer fits: measure again
@@ -83,7 +88,7 @@ class TileCache:
             near = [r for r, t in times.items() if r > 0 and t <= fastest * (1 + BATCH_MARGIN)]
             if near and max(near) != rows:
                 rows = max(near)
-                h.set_tile_rows(algo, rows)
+                self._set(h, algo, rows)
         self.entries[k] = {"rows": rows, "ms": {str(r): t for r, t in times.items()}}
         self.tuned += 1
         return rows
@@ -96,7 +101,7 @@ class TileCache:
             if kk not in chosen:
                 chosen[kk] = self.apply(h, algo)
             else:
-                h.set_tile_rows(algo, chosen[kk])
+                self._set(h, algo, chosen[kk])
             out.append(chosen[kk])
         return out
 
