@@ -72,41 +72,45 @@ __global__ void __launch_bounds__(256) cost_kernel(TableArgs a) {
 //
 // With G = F[p][p] (G[a][b] = F[p_a][p_b]) and T = G.D^T + G^T.D, every delta of Eq. (2)
 // (with its diagonal term) is
-//   delta(i, j) = T_ij + T_ji - T_ii - T_jj + c_ij,
-// c_ij a sum of six products of the entries of D and G at (i, j), (j, i), (i, i), (j, j)
-// (expanding Eq. (2) and collecting the k = i, j terms).  The two n x n x n products
-// run as v_mfma_i32_32x32x16_i8 on entries shifted to int8 (x - 128), with the shift
-// undone exactly from row sums:
-//   sum_k x_k y_k = sum_k x'_k y'_k + 128 (sum_k x'_k + sum_k y'_k) + 128^2 n.
-// A workgroup takes one start.  Phase 0 stages X = G', Y = D' (int8, rows padded to a
-// multiple of 32 with zeros) in LDS, phase 1 X = (G^T)', Y = (D^T)' (skipped when F and
-// D are both symmetric: then the phases are equal).  Each wave owns pairs of 32 x 32
-// output tiles (I <= J) and accumulates S_ij = T_ij + T_ji in place as
-// X_I.Y_J^T + Y_I.X_J^T over both phases, so the transpose costs nothing.
+//   delta(i, j) = T_ij + T_ji - T_ii - T_jj + (d_ij + d_ji - d_ii - d_jj)(g_ij + g_ji - g_ii - g_jj)
+// (expanding Eq. (2) and collecting the k = i, j terms, which factor).  No delta changes when
+// a constant is added to every entry of F or of D, so the contractions run as
+// v_mfma_i32_32x32x32_i8 on entries minus 128 and nothing is corrected.
+// A workgroup takes one start: X = G, Y = D in LDS (int8, zero past n); a wave takes pairs of
+// 32 x 32 output tiles (I <= J) and accumulates T_ij + T_ji as X_I.Y_J^T + Y_I.X_J^T over the
+// rows and, unless F and D are both symmetric, the same over the columns, which the transposing
+// LDS reads give without a transposed copy.
+// Bound by the gathers and reads of LDS beside the table's own bytes.  1024 starts, us, before
+// (transposed matrices staged in a second phase, the shift undone from row sums, the k = i, j
+// terms from eight byte reads an entry) and now: n = 64 12.8 and 7.9, 101 59.6 and 27.2, 128
+// symmetric 45.9 and 28.4 (33 MB written), 128 66.3 and 32.2, 200 61.5 and 31.3 (256 starts),
+// 256 84.2 and 43.7 (256 starts).
 
+typedef int v2i __attribute__((ext_vector_type(2)));
+typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
 constexpr int TB_LANES = 512, TB_W = TB_LANES / 64;
-constexpr int TB_MAXP = 5;   // tile pairs per wave: 36 pairs at n = 256 over 8 waves
 
 __host__ __device__ inline int tb_rows(int n) { return (n + 31) & ~31; }
+// LDS rows: an odd multiple of 16 bytes
+__host__ __device__ inline int tb_stride(int n) { return (((n + 15) / 16) | 1) * 16; }
 
 struct TbPlan {
-    int perm, pinv, x, y, u, td, total;
+    int perm, pinv, sd, dg, x, y, total;
 };
 
 __host__ __device__ inline TbPlan tb_plan(int n) {
-    const int rs = row_stride(n), np = tb_rows(n);
+    const int rs = tb_stride(n), np = tb_rows(n);
     TbPlan q;
     int o = 0;
     q.perm = o; o += np * 4;
     q.pinv = o; o += np * 4;
-    q.u = o;    o += np * 4;
-    q.td = o;   o += np * 4;
-    o = (o + 255) & ~255;
-    q.x = o;    o += np * rs;
-    o = (o + 255) & ~255;
-    q.y = o;    o += np * rs;
+    q.sd = o;   o += np * 4;   // T_ii
+    q.dg = o;   o += np * 4;   // d_ii | g_ii << 16
+    q.x = o;    o += ((n + 15) & ~15) * rs;
+    q.y = o;    o += ((n + 15) & ~15) * rs;
+    o += 64;                   // the last row's reads past n
     q.total = o;
     return q;
 }
@@ -367,117 +371,119 @@ __global__ void __launch_bounds__(TB_LANES) table_wide_mfma_kernel(TableArgs a) 
 // The whole neighbourhood of one start, perm already in LDS (tb_plan layout at sm).
 __device__ __attribute__((always_inline)) void table_mfma_body(const uint8_t *mats, int n, int sym, unsigned char *sm, int32_t *out) {
     const TbPlan P = tb_plan(n);
-    const int rs = row_stride(n), np = tb_rows(n), nt = np / 32, L = blockDim.x, t = threadIdx.x;
-    const int lane = t & 63, w = t >> 6;
+    const int grs = row_stride(n), rs = tb_stride(n), nr = (n + 15) & ~15, nt = tb_rows(n) / 32, L = blockDim.x,
+              t = threadIdx.x;
+    const int lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6), half = lane >> 5, l5 = lane & 31;
     const int *perm = reinterpret_cast<const int *>(sm + P.perm);
-    int *U = reinterpret_cast<int *>(sm + P.u);
-    int *TD = reinterpret_cast<int *>(sm + P.td);
-    uint8_t *X = sm + P.x, *Y = sm + P.y;
-    const int npairs = nt * (nt + 1) / 2;
-    for (int i = t; i < np; i += L) U[i] = TD[i] = 0;
-
-    v16i acc[TB_MAXP];
+    int *SD = reinterpret_cast<int *>(sm + P.sd), *DG = reinterpret_cast<int *>(sm + P.dg);
+    int8_t *X = reinterpret_cast<int8_t *>(sm + P.x), *Y = reinterpret_cast<int8_t *>(sm + P.y);
+    const int vpr = rs / 16;
+    // 16 bytes of a global row less 128 (bytes past n stay zero)
+    auto biased = [&](const uint8_t *row, int c) -> uint4 {
+        uint4 x = *reinterpret_cast<const uint4 *>(row + c);
+        unsigned m[4];
 #pragma unroll
-    for (int q = 0; q < TB_MAXP; ++q)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[q][r] = 0;
-
-    const int phases = sym ? 1 : 2;
-    for (int ph = 0; ph < phases; ++ph) {
-        const uint8_t *Fp = mats + (size_t)(ph ? 1 : 0) * n * rs;   // F, then F^T
-        const uint8_t *Dp = mats + (size_t)(ph ? 3 : 2) * n * rs;   // D, then D^T
-        // raw rows of F_p into Y, then X[i][k] = F_p[p_i][p_k] - 128 gathered from them
-        const int vec = n * rs / 16;
-        for (int v = t; v < vec; v += L)
-            reinterpret_cast<uint4 *>(Y)[v] = reinterpret_cast<const uint4 *>(Fp)[v];
-        __syncthreads();
-        const int wpr = rs / 4;
-        for (int v = t; v < np * wpr; v += L) {
-            const int i = v / wpr, k0 = (v - i * wpr) * 4;
-            unsigned word = 0;
-            if (i < n) {
-                const uint8_t *row = Y + perm[i] * rs;
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (k0 + e < n) word |= (unsigned)(row[perm[k0 + e]] ^ 0x80u) << (8 * e);
-            }
-            reinterpret_cast<unsigned *>(X)[v] = word;
+        for (int e = 0; e < 4; ++e) {
+            const int real = n - (c + 4 * e);
+            m[e] = real >= 4 ? 0x80808080u : (real <= 0 ? 0u : (0x80808080u >> (8 * (4 - real))));
         }
-        __syncthreads();
-        // Y[i][k] = D_p[i][k] - 128 (the global rows are zero past n: shift real bytes only)
-        const int vpr = rs / 16;
-        for (int v = t; v < np * vpr; v += L) {
-            const int i = v / vpr, c = (v - i * vpr) * 16;
-            uint4 x = make_uint4(0, 0, 0, 0);
-            if (i < n) {
-                x = reinterpret_cast<const uint4 *>(Dp + (size_t)i * rs)[c / 16];
-                unsigned m[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int k = c + 4 * e, real = n - k;   // bytes k .. k+3, real ones first
-                    m[e] = real >= 4 ? 0x80808080u : (real <= 0 ? 0u : (0x80808080u >> (8 * (4 - real))));
-                }
-                x.x ^= m[0]; x.y ^= m[1]; x.z ^= m[2]; x.w ^= m[3];
-            }
-            reinterpret_cast<uint4 *>(Y)[v] = x;
-        }
-        __syncthreads();
-        // per index: the row sums of X' and Y' and the diagonal term sum_k x_ik y_ik
-        for (int i = t; i < n; i += L) {
-            const int *xr = reinterpret_cast<const int *>(X + i * rs), *yr = reinterpret_cast<const int *>(Y + i * rs);
-            int sx = 0, sy = 0, dxy = 0;
-            for (int c = 0; c < rs / 4; ++c) {
-                const int a = xr[c], b = yr[c];
-                sx = __builtin_amdgcn_sdot4(a, 0x01010101, sx, false);
-                sy = __builtin_amdgcn_sdot4(b, 0x01010101, sy, false);
-                dxy = __builtin_amdgcn_sdot4(a, b, dxy, false);
-            }
-            U[i] += sx + sy;
-            TD[i] += dxy + 128 * (sx + sy) + 16384 * n;
-        }
-        // S += X_I . Y_J^T + Y_I . X_J^T over this phase
-        const int row = lane & 31, kh = 8 * (lane >> 5);
-#pragma unroll
-        for (int q = 0; q < TB_MAXP; ++q) {
-            const int pq = w + q * TB_W;
-            if (pq < npairs) {
-                int I, J;
-                tb_pair(pq, nt, I, J);
-                const uint8_t *xi = X + (I * 32 + row) * rs + kh, *yj = Y + (J * 32 + row) * rs + kh;
-                const uint8_t *yi = Y + (I * 32 + row) * rs + kh, *xj = X + (J * 32 + row) * rs + kh;
-                for (int k0 = 0; k0 < n; k0 += 16) {
-                    acc[q] = __builtin_amdgcn_mfma_i32_32x32x16_i8(tb_load8(xi + k0), tb_load8(yj + k0), acc[q], 0, 0, 0);
-                    acc[q] = __builtin_amdgcn_mfma_i32_32x32x16_i8(tb_load8(yi + k0), tb_load8(xj + k0), acc[q], 0, 0, 0);
-                }
-            }
-        }
-        __syncthreads();   // sums visible; X, Y free for the next phase
+        return make_uint4(x.x ^ m[0], x.y ^ m[1], x.z ^ m[2], x.w ^ m[3]);
+    };
+    // rows of F into Y, X = F[p][p] gathered from them, then rows of D into Y
+    for (int v = t; v < n * vpr; v += L) {
+        const int i = v / vpr, c = (v - i * vpr) * 16;
+        *reinterpret_cast<uint4 *>(Y + i * rs + c) = biased(mats + (size_t)i * grs, c);
     }
-
-    // ---- epilogue: delta(i, j) for i < j from the accumulators of this wave.  X and Y
-    //      hold the last phase: G^T and D^T (or G and D when symmetric, then equal to them
-    //      transposed), so G_ab = X[b][a] + 128 and D_ab = Y[b][a] + 128 in both cases.
-    auto gv = [&](int a_, int b_) { return (int)(uint8_t)(X[b_ * rs + a_] ^ 0x80); };
-    auto dv = [&](int a_, int b_) { return (int)(uint8_t)(Y[b_ * rs + a_] ^ 0x80); };
+    __syncthreads();
+    const int wpr = rs / 4;
+    for (int v = t; v < nr * wpr; v += L) {
+        const int i = v / wpr, k0 = (v - i * wpr) * 4;
+        unsigned word = 0;
+        if (i < n && k0 < n) {
+            const uint8_t *row = reinterpret_cast<const uint8_t *>(Y) + perm[i] * rs;
+            const int4 pk = *reinterpret_cast<const int4 *>(perm + k0);   // (entries past n: below)
+            word = row[pk.x];
+            if (k0 + 1 < n) word |= (unsigned)row[pk.y] << 8;
+            if (k0 + 2 < n) word |= (unsigned)row[pk.z] << 16;
+            if (k0 + 3 < n) word |= (unsigned)row[pk.w] << 24;
+        }
+        *reinterpret_cast<unsigned *>(X + i * rs + k0) = word;
+    }
+    __syncthreads();
+    for (int v = t; v < nr * vpr; v += L) {
+        const int i = v / vpr, c = (v - i * vpr) * 16;
+        *reinterpret_cast<uint4 *>(Y + i * rs + c) =
+            i < n ? biased(mats + ((size_t)2 * n + i) * grs, c) : make_uint4(0, 0, 0, 0);
+    }
+    __syncthreads();
+    auto rows16 = [&](const int8_t *m, int row, int k) -> v4i { return *reinterpret_cast<const v4i *>(m + row * rs + k); };
+    // 16 rows from row k of 16 columns from col (the lane's: col + l % 16), by transposing reads
+    // of 8 rows; a lane addresses half a row of the 16 columns
+    const int trow = (lane & 15) >> 1, tcol = (lane & 1) * 8;
+    auto cols16 = [&](const int8_t *m, int k, int col) -> v4i {
+        typedef __attribute__((address_space(3))) v2i *lds2;
+        const v2i a = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds2)(m + (k + trow) * rs + col + tcol));
+        const v2i b = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds2)(m + (k + trow + 8) * rs + col + tcol));
+        return v4i{a[0], a[1], b[0], b[1]};
+    };
+    // T_ii and the diagonals, 32 indices a wave (entries past n are zero)
+    if (w < nt) {
+        const int i = w * 32 + l5, ic = min(i, n - 1);
+        int td = 0;
+        for (int k = 0; k < n; k += 16) {
+            const v4i x = rows16(X, ic, k), y = rows16(Y, ic, k);
 #pragma unroll
-    for (int q = 0; q < TB_MAXP; ++q) {
-        const int pq = w + q * TB_W;
-        if (pq >= npairs) continue;
+            for (int e = 0; e < 4; ++e) td = __builtin_amdgcn_sdot4(x[e], y[e], td, false);
+            if (!sym) {
+                const v4i xc = cols16(X, k, w * 32 + (lane & 16)), yc = cols16(Y, k, w * 32 + (lane & 16));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) td = __builtin_amdgcn_sdot4(xc[e], yc[e], td, false);
+            }
+        }
+        if (!half) {
+            SD[i] = sym ? 2 * td : td;
+            DG[i] = (int)(((unsigned)X[ic * rs + ic] << 16) | ((unsigned)Y[ic * rs + ic] & 0xffffu));
+        }
+    }
+    __syncthreads();
+    const int npairs = nt * (nt + 1) / 2;
+    for (int pq = w; pq < npairs; pq += TB_W) {
         int I, J;
         tb_pair(pq, nt, I, J);
-        const int j = J * 32 + (lane & 31);
+        v16i acc;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int i = I * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-            if (i < j && j < n) {
-                const int s_ij = sym ? 2 * (acc[q][r] + 128 * (U[i] + U[j]) + 32768 * n)
-                                     : acc[q][r] + 128 * (U[i] + U[j]) + 65536 * n;
-                const int t_ii = sym ? 2 * TD[i] : TD[i], t_jj = sym ? 2 * TD[j] : TD[j];
-                const int Dij = dv(i, j), Dji = dv(j, i), Dii = dv(i, i), Djj = dv(j, j);
-                const int Gij = gv(i, j), Gji = gv(j, i), Gii = gv(i, i), Gjj = gv(j, j);
-                const int c = -(Dji - Dii) * (Gii - Gji) - (Djj - Dij) * (Gij - Gjj) - (Dij - Dii) * (Gii - Gij)
-                              - (Djj - Dji) * (Gji - Gjj) + (Dji - Dij) * (Gij - Gji) + (Djj - Dii) * (Gii - Gjj);
-                out[pidx(n, i, j)] = s_ij - t_ii - t_jj + c;
+        for (int r = 0; r < 16; ++r) acc[r] = 0;
+        const int j = J * 32 + l5, jc = min(j, n - 1), ir = min(I * 32 + l5, n - 1);
+        for (int k = 0; k < n; k += 32) {
+            const int kk = min(k + half * 16, nr - 16);
+            const bool in = k + half * 16 < n;
+            v4i xi = rows16(X, ir, kk), yi = rows16(Y, ir, kk);
+            v4i xj = rows16(X, jc, kk), yj = rows16(Y, jc, kk);
+            if (!in) xi = yi = v4i{0, 0, 0, 0};
+            acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(xi, yj, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(yi, xj, acc, 0, 0, 0);
+            if (!sym) {
+                xi = cols16(X, kk, I * 32 + (lane & 16)), yi = cols16(Y, kk, I * 32 + (lane & 16));
+                xj = cols16(X, kk, J * 32 + (lane & 16)), yj = cols16(Y, kk, J * 32 + (lane & 16));
+                if (!in) xi = yi = v4i{0, 0, 0, 0};
+                acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(xi, yj, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(yi, xj, acc, 0, 0, 0);
+            }
+        }
+        // the rows of the lane's slots come four in a row: entries (j, i .. i + 3) are a word
+        const int sj = SD[jc], gj = DG[jc];
+#pragma unroll
+        for (int y = 0; y < 4; ++y) {
+            const int i0 = I * 32 + 8 * y + 4 * half;
+            const v4i si = *reinterpret_cast<const v4i *>(SD + i0), gi = *reinterpret_cast<const v4i *>(DG + i0);
+            const int xw = *reinterpret_cast<const int *>(X + jc * rs + i0), yw = *reinterpret_cast<const int *>(Y + jc * rs + i0);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int i = i0 + e, ic = min(i, n - 1);
+                const int g = (int)X[ic * rs + jc] + (int)(int8_t)(xw >> (8 * e)) - (gi[e] >> 16) - (gj >> 16);
+                const int d = (int)Y[ic * rs + jc] + (int)(int8_t)(yw >> (8 * e)) - (int)(int16_t)gi[e] - (int)(int16_t)gj;
+                const int a = acc[4 * y + e];
+                if (i < j && j < n) out[pidx(n, i, j)] = (sym ? 2 * a : a) - si[e] - sj + __mul24(d, g);
             }
         }
     }
