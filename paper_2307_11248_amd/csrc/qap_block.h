@@ -176,6 +176,9 @@ struct Tenures {
 // it and selecting (the sixteen slots of a block each time).
 __device__ inline void stay_branch() { asm volatile(""); }
 
+// waits for the wave's own global stores and atomics (vmcnt 0)
+__device__ inline void vm_done() { __builtin_amdgcn_s_waitcnt(0x0f70); }
+
 // (called by one lane; the address is opaque, so that no cross-lane reduction is put around it)
 __device__ inline void sel_min(long long *slot, int d, int key) {
     int z = 0;
@@ -188,14 +191,19 @@ __device__ inline void sel_min(long long *slot, int d, int key) {
 // them once).
 struct BlkShared {
     long long sel[2];      // the minimum over the waves, by iteration parity
+    long long dsel;        // diversification: the lowest (count, key)
+    int ddelta;            // and its delta
+    int pad;
     long long red[8];
     int ev[68];            // the number of pairs that become free, then the pairs
     int bad, chunk_end;
 };
 
-template <int NB, bool SYM, bool TABU, bool RESUME, bool BUSY>
+// FREQ: tabu that keeps the frequency memory (a.freq), with the diversification move (a.div)
+// and, for a.attr 1, marked units in place of tabu pairs.
+template <int NB, bool SYM, bool TABU, bool RESUME, bool BUSY, bool FREQ>
 __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigned char *sm, BlkShared &sh) {
-    static_assert(TABU || !RESUME, "forms in use");
+    static_assert((TABU || !RESUME) && (!FREQ || (TABU && !RESUME && !BUSY)), "forms in use");
     using SH = Shape<NB>;
     constexpr int KS = SH::KS, L = SH::LANES, TW = SH::TW, TC = SH::TC, BPW = SH::BPW, NP = NB * 32;
     constexpr bool SW = SH::SW;
@@ -218,6 +226,10 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
     int *const perm = reinterpret_cast<int *>(sm + P.perm), *const bestp = reinterpret_cast<int *>(sm + P.bestp);
     unsigned *const bits = reinterpret_cast<unsigned *>(sm + P.bits);
     int *const ring = reinterpret_cast<int *>(sm + P.ring);
+    // unit marking: until when the unit at a location is marked (the pairs' bits are not used
+    // then); a slot is tabu while either of its units is
+    const bool marks = FREQ && a.attr == 1;
+    int *const mark = reinterpret_cast<int *>(sm + P.bits);
     SearchState *const st = RESUME ? a.st : nullptr;
     const bool resume = RESUME && st->it > 1;
 
@@ -248,6 +260,12 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
     if (!SYM)
         for (int i = t; i < 4 * 64 * KS / 4; i += L) reinterpret_cast<int *>(side)[i] = 0;
     if (t < 2) sel[t] = BK_NONE;
+    if (FREQ) {
+        if (t == 0) sh.dsel = BK_NONE;
+        if (t == 0) s_ev[0] = 0;
+        for (int i = t; i < a.m; i += L) a.freq[i] = 0;
+        vm_done();   // before the adds of the housekeeping wave
+    }
     __syncthreads();
     const int32_t *const pin = resume ? a.st_perm : a.perm_in;
     for (int u = t; u < n; u += L) {
@@ -354,11 +372,29 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
     // chunk) ends here
     int r = 0, s = 0, dstar = 0;
     bool improved = false, stopped = false;
-    auto next_move = [&]() -> bool {
+    int last_imp = 0;   // FREQ: the iteration of the last new best or diversification
+    // scan, publish (FREQ, block waves): the lowest (count, key) of the wave's free slots into
+    // sh.dsel; the delta of the pair `key`, if the wave holds it, into sh.ddelta
+    auto next_move_from = [&](auto scan, auto publish) -> bool {
         const long long mk = sel[it & 1];
         if (RESUME && __builtin_amdgcn_readfirstlane(s_chunk_end)) return false;
         dstar = __builtin_amdgcn_readfirstlane((int)(mk >> 32));
-        const int key = __builtin_amdgcn_readfirstlane((int)mk);
+        int key = __builtin_amdgcn_readfirstlane((int)mk);
+        bool diversified = false;
+        if (FREQ && a.div > 0 && it - last_imp > a.div) {
+            // the free pair exchanged least often so far, the lowest key among equals
+            scan();
+            __syncthreads();
+            const long long best2 = sh.dsel;
+            if (__builtin_amdgcn_readfirstlane((int)(best2 >> 32)) != INT32_MAX) {   // else every move is tabu
+                key = __builtin_amdgcn_readfirstlane((int)best2);
+                publish(key);
+                __syncthreads();
+                dstar = __builtin_amdgcn_readfirstlane(sh.ddelta);
+                diversified = true;
+                if (wid == TW && lane == 0) sh.dsel = BK_NONE;   // (read by all before the barrier)
+            }
+        }
         if (TABU ? dstar == INT32_MAX : dstar >= 0) {
             stopped = true;
             return false;
@@ -368,8 +404,10 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
         gap += dstar;
         improved = TABU && gap < 0;
         if (improved) gap = 0;
+        if (FREQ && (improved || diversified)) last_imp = it;
         return true;
     };
+    auto next_move = [&]() -> bool { return next_move_from([] {}, [](int) {}); };
     // aspiration threshold of the next select: a tabu move is allowed below it
     auto aspire = [&]() -> int { return max(-gap, -(1 << 24)); };
 
@@ -480,7 +518,10 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
 #pragma unroll
             for (int c = 0; c < TC; ++c) {
                 guu[c] = G[at(ucl[c], ucl[c])];
-                tb[c] = TABU && wid * TC + c < NB ? bits[b * NB + wid * TC + c] : 0u;
+                if (marks)
+                    tb[c] = mark[ucl[c]] > it + 1 || mark[b] > it + 1 ? ~0u : 0u;
+                else
+                    tb[c] = TABU && wid * TC + c < NB ? bits[b * NB + wid * TC + c] : 0u;
             }
             asm volatile("" ::: "memory");   // those first: they come back with the rows below
             v4i cc[TC][2], cs = {0, 0, 0, 0};
@@ -561,7 +602,7 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
                 if (u == r || u == s) dl = -dstar;       // the move undone
                 const bool real = u < n && u != b;
                 const bool tabu = TABU && ((tb[c] >> l5) & 1u);
-                if (TC * TW == NB || u < NP) rp[half * NP + u] = !real ? BK_NOMOVE : (tabu ? dl + BK_OFF : dl - BK_OFF);
+                if (TC * TW == NB || u < NP) rp[half * NP + u] = !real ? BK_NOMOVE : (tabu && !marks ? dl + BK_OFF : dl - BK_OFF);
                 const bool adm = real && (!tabu || dl < thr);
                 const int dc = adm ? dl : INT32_MAX, kc = (min(u, b) << 9) | max(u, b);
                 if (c == 0) {
@@ -601,7 +642,7 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
             if (myev >= 0) s_ev[1 + __builtin_popcountll(m & ((1ull << lane) - 1))] = myev;
             if (lane == 0) s_ev[0] = c;
         };
-        if (TABU) find_events(it + 1, it - 1);
+        if (TABU && !marks) find_events(it + 1, it - 1);
         // tenures of iterations it .. it + 63 (lane i: it + i), and the next ones in the making
         Tenures next;
         int tens = 0, tpos = 0;
@@ -618,12 +659,13 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
             // chunk end: decided every 16 iterations, read by every wave after B1
             if (RESUME && clock_end != 0 && it != it_first && (it & 15) == 0 && lane == 0)
                 s_chunk_end = (long long)wall_clock64() >= clock_end;
+            if (FREQ && a.div > 0) vm_done();   // the move before is counted
             __syncthreads();   // B1
             if (!next_move()) break;
             cur += dstar;
             // ---- A
             if (lane == 0) sel[(it + 1) & 1] = BK_NONE;
-            const unsigned was = TABU ? bits[r * NB + (s >> 5)] : 0u;
+            const unsigned was = TABU && !marks ? bits[r * NB + (s >> 5)] : 0u;
             if (lane < 4) {    // the corners of G: (r, r), (r, s), (s, r), (s, s) take (sigma, sigma)
                 const int i = lane & 2 ? s : r, j = lane & 1 ? s : r;
                 const int si = lane & 2 ? r : s, sj = lane & 1 ? r : s;
@@ -635,7 +677,11 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
                 best = cur;
                 for (int x = lane; x < n; x += 64) bestp[x] = perm[x == r ? s : (x == s ? r : x)];
             }
-            if (TABU) {
+            if (FREQ && lane == 0)
+                __hip_atomic_fetch_add(a.freq + pidx(n, r, s), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (marks) {   // the two units moved now sit at s and r
+                if (lane < 2) mark[lane ? s : r] = it + tn;
+            } else if (TABU) {
                 const int pr = (r << 9) | s;
                 if (myev >= 0) {
                     const int x = myev >> 9, y = myev & 511;
@@ -666,7 +712,7 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
                 perm[s] = x;
             }
             if (TABU) {
-                find_events(it + 2, it);
+                if (!marks) find_events(it + 2, it);
                 if (tpos < 10) next.round();
                 if (++tpos == 64) {
                     tpos = 0;
@@ -762,7 +808,7 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
                 acc[q][i] = x < n && v < n && x != v ? full - BK_OFF : BK_NOMOVE;
             }
         }
-        // candidate of the wave's blocks into sel[x], columns er and es left out
+        // candidate of the wave's blocks for iteration x into sel, columns er and es left out
         auto candidates = [&](int er, int es, int x, int thr) {
             const int thrk = (thr - BK_OFF) * 32;
             int cand = INT32_MAX, base = (bI[0] << 14) | (bJ[0] << 5);   // of the candidate's block
@@ -780,7 +826,19 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
                     if (TABU) um = min(min(um, (unsigned)k[i]), (unsigned)k[i + 1]);
                 }
                 int c = lo_;
-                if (TABU) {
+                if (marks) {
+                    // every slot is held as free: the lowest of all where it is below the
+                    // threshold, else the lowest with neither unit marked
+                    int f = INT32_MAX;
+#pragma unroll
+                    for (int y = 0; y < 4; ++y) {
+                        const v4i mr = *reinterpret_cast<const v4i *>(mark + bI[q] * 32 + 8 * y + 4 * half);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) f = min(f, mr[e] > x ? INT32_MAX : k[4 * y + e]);
+                    }
+                    if (mark[bJ[q] * 32 + l5] > x) f = INT32_MAX;
+                    c = lo_ < thrk ? lo_ : f;
+                } else if (TABU) {
                     const int ta = (int)(um ^ 0x80000000u);   // the lowest tabu slot, as if free
                     c = ta < thrk ? min(lo_, ta) : lo_;
                 }
@@ -801,7 +859,7 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
                 const int wm = wmin32(cand);
                 if (wm < 0) {   // lanes that tie hold the same row: the lowest column
                     const int ln = (int)__builtin_ctzll(__ballot(cand == wm));
-                    if (lane == 0) sel_min(&sel[x], (wm >> 5) + BK_OFF, base + ((wm & 31) << 9) + (ln & 31));
+                    if (lane == 0) sel_min(&sel[x & 1], (wm >> 5) + BK_OFF, base + ((wm & 31) << 9) + (ln & 31));
                 }
             } else {
                 const int d = cand >> 5, wd = wmin32(d), key = base + ((cand & 31) << 9) + l5;
@@ -810,7 +868,7 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
                     const int wk = __builtin_popcountll(tie) == 1
                                        ? __builtin_amdgcn_readlane(key, (int)__builtin_ctzll(tie))
                                        : wmin32(d == wd ? key : KEY_NONE);
-                    if (lane == 0) sel_min(&sel[x], wd + BK_OFF, wk);
+                    if (lane == 0) sel_min(&sel[x & 1], wd + BK_OFF, wk);
                 }
             }
         };
@@ -855,7 +913,7 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
                 }
             }
         };
-        candidates(-1, -1, it & 1, aspire());
+        candidates(-1, -1, it, aspire());
         while (it <= cap) {
             __syncthreads();   // B1
             // what A needs beside the move, read together with it
@@ -867,7 +925,45 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
                 }
             v4i ev = {0, 0, 0, 0};
             if (TABU) ev = *reinterpret_cast<const v4i *>(s_ev);
-            if (!next_move()) break;
+            const auto scan = [&] {
+                patch();                 // nothing stale may be chosen
+                r0 = s0 = NOWHERE;
+                long long low = BK_NONE;
+#pragma unroll
+                for (int q = 0; q < BPW; ++q) {
+                    if (!has(q)) break;
+                    const int v = bJ[q] * 32 + l5;
+#pragma unroll 1
+                    for (int i = 0; i < 16; ++i) {
+                        const int x = bI[q] * 32 + 8 * (i >> 2) + 4 * half + (i & 3), val = acc[q][i];
+                        // (free slots are moves; a mirror slot loses to its pair's own)
+                        if (val < 0 && !(marks && (mark[x] > it || mark[v] > it))) {
+                            const int cnt = __hip_atomic_load(a.freq + pidx(n, min(x, v), max(x, v)), __ATOMIC_RELAXED,
+                                                              __HIP_MEMORY_SCOPE_AGENT);
+                            const long long c = ((long long)cnt << 32) | (unsigned)((x << 9) | v);
+                            low = c < low ? c : low;
+                        }
+                    }
+                }
+                if (low != BK_NONE) sel_min(&sh.dsel, (int)(low >> 32), (int)low);
+            };
+            const auto publish = [&](int key) {
+                const int x = key >> 9, y = key & 511;
+                const unsigned me = in_row(x) & in_col(y);
+#pragma unroll
+                for (int q = 0; q < BPW; ++q)
+                    if (has(q) && ((me >> q) & 1)) {
+                        stay_branch();
+                        const int i = ((x >> 3) & 3) * 4 + (x & 3), val = acc[q][i];
+                        if (half == ((x >> 2) & 1) && l5 == (y & 31)) sh.ddelta = val + BK_OFF;
+                    }
+            };
+            bool go;
+            if constexpr (FREQ)
+                go = next_move_from(scan, publish);
+            else
+                go = next_move();
+            if (!go) break;
             const int thr = aspire();
             // ---- A
             patch();
@@ -919,7 +1015,7 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
                 acc[q] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wa, wx, acc[q], 0, 0, 0);
             }
             __builtin_amdgcn_s_setprio(0);
-            candidates(r, s, (it + 1) & 1, thr);
+            candidates(r, s, it + 1, thr);
             r0 = r;
             s0 = s;
             ++it;
@@ -970,7 +1066,7 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
 // (NB <= 4): held to 64 VGPRs, so that two and more searches share a compute unit, for
 // launches of more searches than compute units; else a task wave keeps more of its
 // operands in flight.
-template <int NB, bool SYM, bool TABU, bool BUSY>
+template <int NB, bool SYM, bool TABU, bool BUSY, bool FREQ>
 __global__ void __launch_bounds__(Shape<NB>::LANES) __attribute__((amdgpu_waves_per_eu(BUSY ? 8 : 4)))
 block_kernel(SearchArgs a, BatchArgs b) {
     extern __shared__ __align__(16) unsigned char sm[];
@@ -997,39 +1093,45 @@ block_kernel(SearchArgs a, BatchArgs b) {
         it.seed = a.seed;
         it.start_id = a.start_base + job;
         it.blk = a.blk;
+        if (FREQ) {
+            it.m = a.m;
+            it.freq = a.freq + (size_t)job * a.m;
+            it.div = a.div;
+            it.attr = a.attr;
+        }
     }
-    block_body<NB, SYM, TABU, false, BUSY>(it, sm, sh);
+    block_body<NB, SYM, TABU, false, BUSY, FREQ>(it, sm, sh);
 }
 
-template <int NB, bool SYM, bool TABU, bool BUSY>
+template <int NB, bool SYM, bool TABU, bool BUSY, bool FREQ>
 hipError_t launch_nb(const SearchArgs &a, const BatchArgs &b, int grid, size_t smem, hipStream_t st) {
-    hipLaunchKernelGGL((block_kernel<NB, SYM, TABU, BUSY>), dim3(grid), dim3(Shape<NB>::LANES), smem, st, a, b);
+    hipLaunchKernelGGL((block_kernel<NB, SYM, TABU, BUSY, FREQ>), dim3(grid), dim3(Shape<NB>::LANES), smem, st, a, b);
     return report(hipGetLastError(), "block kernel launch");
 }
 
-template <bool TABU, bool BUSY>
+template <bool TABU, bool BUSY, bool FREQ = false>
 hipError_t launch_any(int form, const SearchArgs &a, const BatchArgs &b, int grid, size_t smem, hipStream_t st) {
     switch (form) {
-        case 0: return launch_nb<1, false, TABU, BUSY>(a, b, grid, smem, st);
-        case 1: return launch_nb<1, true, TABU, BUSY>(a, b, grid, smem, st);
-        case 2: return launch_nb<2, false, TABU, BUSY>(a, b, grid, smem, st);
-        case 3: return launch_nb<2, true, TABU, BUSY>(a, b, grid, smem, st);
-        case 4: return launch_nb<3, false, TABU, BUSY>(a, b, grid, smem, st);
-        case 5: return launch_nb<3, true, TABU, BUSY>(a, b, grid, smem, st);
-        case 6: return launch_nb<4, false, TABU, BUSY>(a, b, grid, smem, st);
-        case 7: return launch_nb<4, true, TABU, BUSY>(a, b, grid, smem, st);
+        case 0: return launch_nb<1, false, TABU, BUSY, FREQ>(a, b, grid, smem, st);
+        case 1: return launch_nb<1, true, TABU, BUSY, FREQ>(a, b, grid, smem, st);
+        case 2: return launch_nb<2, false, TABU, BUSY, FREQ>(a, b, grid, smem, st);
+        case 3: return launch_nb<2, true, TABU, BUSY, FREQ>(a, b, grid, smem, st);
+        case 4: return launch_nb<3, false, TABU, BUSY, FREQ>(a, b, grid, smem, st);
+        case 5: return launch_nb<3, true, TABU, BUSY, FREQ>(a, b, grid, smem, st);
+        case 6: return launch_nb<4, false, TABU, BUSY, FREQ>(a, b, grid, smem, st);
+        case 7: return launch_nb<4, true, TABU, BUSY, FREQ>(a, b, grid, smem, st);
         default: break;
     }
     if constexpr (!BUSY)
         switch (form) {
-            case 8: return launch_nb<5, false, TABU, false>(a, b, grid, smem, st);
-            case 9: return launch_nb<5, true, TABU, false>(a, b, grid, smem, st);
-            case 10: return launch_nb<6, false, TABU, false>(a, b, grid, smem, st);
-            case 11: return launch_nb<6, true, TABU, false>(a, b, grid, smem, st);
-            case 12: return launch_nb<7, false, TABU, false>(a, b, grid, smem, st);
-            case 13: return launch_nb<7, true, TABU, false>(a, b, grid, smem, st);
-            case 14: return launch_nb<8, false, TABU, false>(a, b, grid, smem, st);
-            case 15: return launch_nb<8, true, TABU, false>(a, b, grid, smem, st);
+            case 8: return launch_nb<5, false, TABU, false, FREQ>(a, b, grid, smem, st);
+            case 9: return launch_nb<5, true, TABU, false, FREQ>(a, b, grid, smem, st);
+            case 10: return launch_nb<6, false, TABU, false, FREQ>(a, b, grid, smem, st);
+            case 11: return launch_nb<6, true, TABU, false, FREQ>(a, b, grid, smem, st);
+            case 12: return launch_nb<7, false, TABU, false, FREQ>(a, b, grid, smem, st);
+            case 13: return launch_nb<7, true, TABU, false, FREQ>(a, b, grid, smem, st);
+            case 14: return launch_nb<8, false, TABU, false, FREQ>(a, b, grid, smem, st);
+            case 15: return launch_nb<8, true, TABU, false, FREQ>(a, b, grid, smem, st);
             default: break;
         }
     return hipErrorInvalidValue;

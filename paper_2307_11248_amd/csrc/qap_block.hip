@@ -22,12 +22,14 @@ int block_ok(int n, int sym, int blk, bool tabu, int lo, int hi, size_t max_smem
 
 hipError_t launch_block_busy(bool tabu, int form, const SearchArgs &a, const BatchArgs &b, int grid, size_t smem,
                              hipStream_t st);   // qap_block_busy.hip
+hipError_t launch_block_freq(int form, const SearchArgs &a, int grid, size_t smem, hipStream_t st);   // qap_block_freq.hip
 
 hipError_t launch_block(bool tabu, int form, bool busy, size_t smem, const SearchArgs *a, const BatchArgs *b, int grid,
                         hipStream_t st) {
     if (grid <= 0) return hipSuccess;
     const SearchArgs sa = a ? *a : SearchArgs{};
     const BatchArgs ba = b ? *b : BatchArgs{};
+    if (sa.freq) return launch_block_freq(form, sa, grid, smem, st);
     if (busy && form < 2 * 4) return launch_block_busy(tabu, form, sa, ba, grid, smem, st);
     return tabu ? launch_any<true, false>(form, sa, ba, grid, smem, st)
                 : launch_any<false, false>(form, sa, ba, grid, smem, st);

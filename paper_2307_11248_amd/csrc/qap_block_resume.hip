@@ -12,22 +12,22 @@ __global__ void __launch_bounds__(1024) resume_block_kernel(const Item *items) {
     __shared__ __align__(16) BlkShared sh;
     const Item it = items[blockIdx.x];
     switch ((it.n + 31) / 32 * 2 + (it.sym ? 1 : 0)) {
-        case 2: block_body<1, false, true, true, false>(it, sm, sh); break;
-        case 3: block_body<1, true, true, true, false>(it, sm, sh); break;
-        case 4: block_body<2, false, true, true, false>(it, sm, sh); break;
-        case 5: block_body<2, true, true, true, false>(it, sm, sh); break;
-        case 6: block_body<3, false, true, true, false>(it, sm, sh); break;
-        case 7: block_body<3, true, true, true, false>(it, sm, sh); break;
-        case 8: block_body<4, false, true, true, false>(it, sm, sh); break;
-        case 9: block_body<4, true, true, true, false>(it, sm, sh); break;
-        case 10: block_body<5, false, true, true, false>(it, sm, sh); break;
-        case 11: block_body<5, true, true, true, false>(it, sm, sh); break;
-        case 12: block_body<6, false, true, true, false>(it, sm, sh); break;
-        case 13: block_body<6, true, true, true, false>(it, sm, sh); break;
-        case 14: block_body<7, false, true, true, false>(it, sm, sh); break;
-        case 15: block_body<7, true, true, true, false>(it, sm, sh); break;
-        case 16: block_body<8, false, true, true, false>(it, sm, sh); break;
-        default: block_body<8, true, true, true, false>(it, sm, sh); break;
+        case 2: block_body<1, false, true, true, false, false>(it, sm, sh); break;
+        case 3: block_body<1, true, true, true, false, false>(it, sm, sh); break;
+        case 4: block_body<2, false, true, true, false, false>(it, sm, sh); break;
+        case 5: block_body<2, true, true, true, false, false>(it, sm, sh); break;
+        case 6: block_body<3, false, true, true, false, false>(it, sm, sh); break;
+        case 7: block_body<3, true, true, true, false, false>(it, sm, sh); break;
+        case 8: block_body<4, false, true, true, false, false>(it, sm, sh); break;
+        case 9: block_body<4, true, true, true, false, false>(it, sm, sh); break;
+        case 10: block_body<5, false, true, true, false, false>(it, sm, sh); break;
+        case 11: block_body<5, true, true, true, false, false>(it, sm, sh); break;
+        case 12: block_body<6, false, true, true, false, false>(it, sm, sh); break;
+        case 13: block_body<6, true, true, true, false, false>(it, sm, sh); break;
+        case 14: block_body<7, false, true, true, false, false>(it, sm, sh); break;
+        case 15: block_body<7, true, true, true, false, false>(it, sm, sh); break;
+        case 16: block_body<8, false, true, true, false, false>(it, sm, sh); break;
+        default: block_body<8, true, true, true, false, false>(it, sm, sh); break;
     }
 }
 

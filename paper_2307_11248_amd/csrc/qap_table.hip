@@ -82,7 +82,7 @@ __global__ void __launch_bounds__(256) cost_kernel(TableArgs a) {
 // LDS reads give without a transposed copy.
 // Bound by the gathers and reads of LDS beside the table's own bytes.  1024 starts, us, before
 // (transposed matrices staged in a second phase, the shift undone from row sums, the k = i, j
-// terms from eight byte reads an entry) and now: n = 64 12.8 and 7.9, 101 59.6 and 27.2, 128
+// terms from eight byte reads an entry) and now: n = 64 (256 starts) 12.8 and 7.9, 101 59.6 and 27.2, 128
 // symmetric 45.9 and 28.4 (33 MB written), 128 66.3 and 32.2, 200 61.5 and 31.3 (256 starts),
 // 256 84.2 and 43.7 (256 starts).
 

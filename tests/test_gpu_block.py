@@ -51,8 +51,8 @@ def instance(n, sym, diag, hiF, hiD):
 
 
 # sizes at the edges of blocks (32), row steps (16 and 64 bytes), workgroup shapes (blocks
-# per wave change above 128, 160, 192 and 224) and LDS layouts (general instances above 176
-# read D from global memory; above 224 the rows are exactly 256 bytes)
+# per wave change above 128, 160, 192 and 224) and LDS layouts (above 224 the rows are exactly
+# 256 bytes)
 SIZES = [2, 3, 16, 31, 32, 33, 48, 63, 64, 65, 95, 96, 97, 127, 128, 129, 144, 159, 160, 161, 176, 177, 191, 192, 193,
          208, 223, 224, 225, 240, 241, 255, 256]
 
@@ -218,3 +218,36 @@ def test_block_served_in_chunks():
                list(enumerate(want)))
     for c, g, r in zip(cases, got, res):
         assert (g[0] == r[0]).all() and g[1] == r[1] and g[2] == r[2], c
+
+
+# the frequency memory: alone, with diversification moves (also as often as every iteration,
+# and where every move is tabu), with marked units; every workgroup shape, hi - lo at the
+# limit of the block form and past it, a start that is no permutation
+@pytest.mark.parametrize("n,sym", [(4, False), (12, True), (32, False), (33, True), (64, False), (81, True), (96, False),
+                                   (128, True), (129, False), (160, True), (161, False), (192, True), (193, False),
+                                   (224, True), (225, False), (256, True), (256, False)])
+@pytest.mark.parametrize("attr,div", [(0, 0), (0, 1), (0, 9), (1, 0), (1, 7)])
+def test_block_frequency_memory(n, sym, attr, div):
+    import torch
+    note("block frequency memory n=%d sym=%d attr=%d div=%d" % (n, sym, attr, div))
+    F, D, rng = instance(n, sym, True, 99, 255)
+    k, iters, seed = 4, 220, 17
+    perms = W.starts(rng, n, k)
+    bad = perms.copy()
+    bad[2, 1] = bad[2, 0]
+    lo, hi = W.tabu_tenure_range(n) if attr == 0 else (3, 3 + n // 10)
+    if n == 12:
+        lo, hi = 0, 64
+    with qap.Handle(F, D) as h:
+        p = torch.from_numpy(bad).cuda()
+        c = torch.zeros(k, dtype=torch.int64, device="cuda")
+        d = torch.zeros(k, dtype=torch.int32, device="cuda")
+        f = torch.full((k, n * (n - 1) // 2), -1, dtype=torch.int32, device="cuda")
+        h.tabu_freq_async(p, iters, lo, hi, seed, c, f, d, div=div, attr=attr)
+        torch.cuda.synchronize()
+        p, c, d, f = p.cpu().numpy(), c.cpu().numpy(), d.cpu().numpy(), f.cpu().numpy()
+    good = [0, 1, 3]
+    ref = pmap(lambda j: oracle.tabu_freq(F, D, perms[j], iters, lo, hi, seed, start=j, div=div, attr=attr), good)
+    for j, r in zip(good, ref):
+        assert (p[j] == r[0]).all() and c[j] == r[1] and d[j] == r[2] and (f[j] == r[3]).all(), j
+    assert (p[2] == bad[2]).all() and c[2] == np.iinfo(np.int64).min and d[2] == qap.QAP_E_NOT_PERM
