@@ -1,7 +1,6 @@
 // qap_table.hip -- cost (Eq. 1) and whole-neighbourhood (Eq. 2) kernels.
 //
-// One workgroup per start.  F and D are staged in LDS as u8 (every entry lies in
-// [0, 255]); the start's permutation and its inverse are staged beside them.
+// One workgroup per start; every entry of F and D lies in [0, 255].
 #include "qap_internal.h"
 
 namespace qapk {
@@ -13,51 +12,64 @@ __device__ inline long long wave_sum64(long long v) {
     return v;
 }
 
-// Stage F and D (global matrices 0 and 2) and one permutation; returns false if the row
-// is not a permutation of 0..n-1.  Ends with a barrier.
-__device__ bool stage_f_d_perm(const TableArgs &a, int job, uint8_t *Fm, uint8_t *Dm, int *perm,
-                               int *pinv, int *bad) {
-    const int n = a.n, rs = row_stride(n), L = blockDim.x, t = threadIdx.x;
-    const int per = n * rs / 16;
-    const uint4 *src = reinterpret_cast<const uint4 *>(a.mats);
-    for (int i = t; i < per; i += L) {
-        reinterpret_cast<uint4 *>(Fm)[i] = src[i];
-        reinterpret_cast<uint4 *>(Dm)[i] = src[2 * per + i];
+// costs[j] = sum_i sum_k F[p_i][p_k] D[i][k]   (Eq. 1)
+//
+// The lane's share of Eq. (1) of one start, 256 lanes: half a wave takes a row, a lane four
+// columns at a time, so that a lane's columns of p stay in registers and its work is four byte
+// gathers a word of D, which is read from global memory in order.  (One lane a row, its
+// columns one after the other, left 155 of 256 lanes idle at n = 101 and made 101 steps of
+// three reads instead of 13 of five.)  us a call, before and now, where a call's host work is
+// 7.9: 1024 starts n = 101 8.8 and 7.9, n = 128 11.1 and 8.1, 256 starts n = 256 12.1 and 9.0,
+// n = 512 177 and 43.
+__device__ __attribute__((always_inline)) inline int cost_part(int n, int rs, const uint8_t *F, const uint8_t *D,
+                                                               const int *perm) {
+    const int t = threadIdx.x;
+    int acc = 0;   // at most 64 rows of 16 entries below 2^16
+    for (int c = (t & 31) * 4; c < n; c += 128) {
+        int pc[4];
+        unsigned in = 0;   // the columns below n
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            pc[e] = c + e < n ? perm[c + e] : 0;
+            if (c + e < n) in |= 0xffu << (8 * e);
+        }
+#pragma unroll 4
+        for (int i = t >> 5; i < n; i += 8) {
+            const unsigned d = *reinterpret_cast<const unsigned *>(D + i * rs + c) & in;
+            const uint8_t *const f = F + perm[i] * rs;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc += (int)f[pc[e]] * (int)((d >> (8 * e)) & 255u);
+        }
     }
-    if (t == 0) *bad = 0;
-    for (int u = t; u < n; u += L) pinv[u] = -1;
-    __syncthreads();
-    const int32_t *p = a.perms + (size_t)job * n;
-    for (int u = t; u < n; u += L) {
-        const int v = p[u];
-        perm[u] = v;
-        if (v < 0 || v >= n || atomicExch(&pinv[v], u) != -1) *bad = 1;
-    }
-    __syncthreads();
-    return *bad == 0;
+    return acc;
 }
 
-// costs[j] = sum_i sum_k F[p_i][p_k] D[i][k]   (Eq. 1)
+// The start and F (bytes) in LDS.  Bound by latency: the launch, the staging and the gathers.
 __global__ void __launch_bounds__(256) cost_kernel(TableArgs a) {
     extern __shared__ __align__(16) unsigned char sm[];
     __shared__ int bad;
     __shared__ long long red[4];
     const int n = a.n, rs = row_stride(n), job = blockIdx.x, t = threadIdx.x;
-    uint8_t *Fm = sm, *Dm = sm + n * rs;
-    int *perm = reinterpret_cast<int *>(sm + 2 * n * rs);
+    uint8_t *Fm = sm;
+    int *perm = reinterpret_cast<int *>(sm + n * rs);
     int *pinv = perm + n;
-    const bool ok = stage_f_d_perm(a, job, Fm, Dm, perm, pinv, &bad);
-    if (!ok) {
+    const int32_t *const p = a.perms + (size_t)job * n;
+    const int mine = t < n ? p[t] : 0;   // n <= 256
+    const uint4 *src = reinterpret_cast<const uint4 *>(a.mats);
+    for (int i = t; i < n * rs / 16; i += 256) reinterpret_cast<uint4 *>(Fm)[i] = src[i];
+    if (t == 0) bad = 0;
+    if (t < n) {
+        pinv[t] = -1;
+        perm[t] = mine;
+    }
+    __syncthreads();
+    if (t < n && (mine < 0 || mine >= n || atomicExch(&pinv[mine], t) != -1)) bad = 1;
+    __syncthreads();
+    if (bad) {
         if (t == 0) a.costs[job] = INT64_MIN;
         return;
     }
-    long long part = 0;
-    for (int i = t; i < n; i += blockDim.x) {
-        const uint8_t *frow = Fm + perm[i] * rs, *drow = Dm + i * rs;
-        int acc = 0;
-        for (int k = 0; k < n; ++k) acc += (int)frow[perm[k]] * (int)drow[k];
-        part += acc;
-    }
+    long long part = cost_part(n, rs, Fm, a.mats + (size_t)2 * n * rs, perm);
     part = wave_sum64(part);
     if ((t & 63) == 0) red[t >> 6] = part;
     __syncthreads();
@@ -145,14 +157,7 @@ __global__ void __launch_bounds__(256) cost_wide_kernel(TableArgs a) {
         if (t == 0) a.costs[job] = INT64_MIN;
         return;
     }
-    const uint8_t *F = a.mats, *D = a.mats + (size_t)2 * n * rs;
-    long long part = 0;
-    for (int i = t; i < n; i += blockDim.x) {
-        const uint8_t *frow = F + (size_t)perm[i] * rs, *drow = D + (size_t)i * rs;
-        int acc = 0;   // at most n * 255^2 < 2^31
-        for (int k = 0; k < n; ++k) acc += (int)frow[perm[k]] * (int)drow[k];
-        part += acc;
-    }
+    long long part = cost_part(n, rs, a.mats, a.mats + (size_t)2 * n * rs, perm);
     part = wave_sum64(part);
     if ((t & 63) == 0) red[t >> 6] = part;
     __syncthreads();
@@ -537,7 +542,7 @@ __global__ void __launch_bounds__(TB_LANES) table_items_kernel(const Item *items
 
 size_t table_smem(int n) { return (size_t)tb_plan(n).total; }
 
-size_t cost_smem(int n) { return (size_t)2 * n * row_stride(n) + (size_t)2 * n * 4; }
+size_t cost_smem(int n) { return (size_t)n * row_stride(n) + (size_t)2 * n * 4; }
 
 }  // namespace
 
