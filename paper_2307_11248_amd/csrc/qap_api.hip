@@ -311,11 +311,15 @@ hipError_t launch_searches(qap_ctx *h, int algo, int32_t *d_perms, const int32_t
 hipError_t launch_shaped(qap_ctx *h, int algo, int ri, SearchArgs a, int k, hipStream_t st, bool plain,
                          const StreamScratch *pre) {
     hipError_t e = hipSuccess;
+    auto streamed = [&](int grid) {
+        return h->block_on[algo] && wide_block_ok(algo != 1, a, h->max_smem) ? launch_wide_block(algo != 1, a, grid, st)
+                                                                             : launch_stream(algo == 0, a, grid, st);
+    };
     if (ri == kStream && pre) {
         a.tile_stride = stream_tile_int4(a.ntiles);
         a.tile_work = pre->tile_work;
         a.job0 = 0;
-        return launch_stream(algo == 0, a, k, st);
+        return streamed(k);
     }
     if (ri == kStream) {
         // tile state in stream-ordered scratch, one slice per search of a launch
@@ -327,11 +331,11 @@ hipError_t launch_shaped(qap_ctx *h, int algo, int ri, SearchArgs a, int k, hipS
         if (plain) {
             for (int j = 0; j < k && e == hipSuccess; ++j) {
                 a.job0 = j;
-                e = launch_stream(algo == 0, a, 1, st);
+                e = streamed(1);
             }
         } else {
             a.job0 = 0;
-            e = launch_stream(algo == 0, a, k, st);
+            e = streamed(k);
         }
         const hipError_t e2 = hipFreeAsync(a.tile_work, st);
         return e != hipSuccess ? e : e2;

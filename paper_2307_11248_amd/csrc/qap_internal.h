@@ -326,6 +326,10 @@ int block_ok(int n, int sym, int blk, bool tabu, int lo, int hi, size_t max_smem
 // (attr 0 or 1, no step record).
 hipError_t launch_block(bool tabu, int form, bool busy, size_t smem, const SearchArgs *a, const BatchArgs *b, int grid,
                         hipStream_t st);
+// Block form above WIDE_N (n to 512), for launches of searches with their tables and the
+// streamed kernels' scratch: whether it serves them, and the launch.
+int wide_block_ok(bool tabu, const SearchArgs &a, size_t max_smem);
+hipError_t launch_wide_block(bool tabu, const SearchArgs &a, int grid, hipStream_t st);
 // One chunk of resumable searches (st != null) of any form: their slots are kept between
 // chunks in st_slots (m int32), their ring of moves in st_ring (block_ring_bytes).
 hipError_t launch_resume_block(const Item *d_items, int count, size_t smem, hipStream_t st);

@@ -251,3 +251,24 @@ def test_block_frequency_memory(n, sym, attr, div):
     for j, r in zip(good, ref):
         assert (p[j] == r[0]).all() and c[j] == r[1] and d[j] == r[2] and (f[j] == r[3]).all(), j
     assert (p[2] == bad[2]).all() and c[2] == np.iinfo(np.int64).min and d[2] == qap.QAP_E_NOT_PERM
+
+
+# above n = 256: block and row-step edges, waves with unequal numbers of blocks, blocks in
+# registers only and in scratch too; the paper's shorter tenures (moves expire), and spans of
+# tenures at the limit of the expiry list and past it
+@pytest.mark.parametrize("n,lohi", [(257, None), (288, (26, 95)), (289, (0, 2)), (320, (30, 157)), (321, (30, 158)),
+                                    (350, None), (352, (2, 20)), (353, (35, 116)), (384, None), (385, (38, 127)),
+                                    (415, None), (416, (3, 9)), (447, (44, 147)), (449, (44, 147)), (480, (5, 60)),
+                                    (481, None), (511, (1, 1)), (512, None), (512, (51, 168))])
+@pytest.mark.parametrize("sym", [False, True])
+def test_wide_block_sizes(n, lohi, sym):
+    note("wide block n=%d tenures %s sym=%d" % (n, lohi, sym))
+    F, D, rng = instance(n, sym, n % 2 == 0, 255 if n % 3 == 0 else 99, 127 if n % 3 == 0 else 255)
+    perms = W.starts(rng, n, 3)
+    lo, hi = lohi or W.tabu_tenure_range(n)
+    iters = 2 * n if n < 300 else 260
+    with qap.Handle(F, D) as h:
+        check_tabu(F, D, perms, iters, lo, hi, 5, h.tabu(perms, iters, lo, hi, 5))
+        p, c, st = h.two_opt(perms, max_iters=60)
+    for j, r in enumerate(pmap(lambda q: oracle.two_opt(F, D, q, max_iters=60), list(perms))):
+        assert (p[j] == r[0]).all() and c[j] == r[1] and st[j] == r[2], j
