@@ -189,7 +189,9 @@ __device__ inline long long tb_load8(const uint8_t *p) { return *reinterpret_cas
 // sums and diagonal terms of those rows, and accumulates the 32 x 32 output tiles of the
 // pair (two per wave) with v_mfma_i32_32x32x16_i8.  The epilogue is the one of the
 // single-block kernel, with the entries of D and G at (i, j), (j, i), (i, i), (j, j)
-// read from global memory.
+// read from global memory.  Bound by the gathers of X: four go out at once, without a branch,
+// beside one word of Y (entry by entry, each behind its test, 256 starts at n = 512 took 860
+// us, symmetric 516, 64 at n = 300 122; now 622, 402 and 87).
 
 constexpr int TW_ROWS = 128;                 // rows of a block
 constexpr int TW_KC = 128;                   // k per chunk
@@ -293,14 +295,16 @@ __global__ void __launch_bounds__(TB_LANES) table_wide_mfma_kernel(TableArgs a) 
                 const int ri = rem / wpr, c = (rem - ri * wpr) * 4;
                 const int i = (side ? BJ : BI) * TW_ROWS + ri, k = k0 + c;
                 unsigned xw = 0, yw = 0;
-                if (i < n) {
-                    const uint8_t *frow = Fp + (size_t)perm[i] * rs, *drow = Dp + (size_t)i * rs;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (k + e < n) {
-                            xw |= (unsigned)(frow[perm[k + e]] ^ 0x80u) << (8 * e);
-                            yw |= (unsigned)(drow[k + e] ^ 0x80u) << (8 * e);
-                        }
+                if (i < n && k < n) {
+                    // (four gathers at once, masked past n, where rows and perm are padded)
+                    const uint8_t *frow = Fp + (size_t)perm[i] * rs;
+                    const int4 pk = *reinterpret_cast<const int4 *>(perm + k);
+                    const int real = n - k;
+                    const unsigned in = real >= 4 ? ~0u : 0xffffffffu >> (8 * (4 - real));
+                    const unsigned f0 = frow[pk.x], f1 = frow[real > 1 ? pk.y : 0], f2 = frow[real > 2 ? pk.z : 0],
+                                   f3 = frow[real > 3 ? pk.w : 0];
+                    xw = ((f0 | f1 << 8 | f2 << 16 | f3 << 24) ^ 0x80808080u) & in;
+                    yw = (*reinterpret_cast<const unsigned *>(Dp + (size_t)i * rs + k) ^ 0x80808080u) & in;
                 }
                 reinterpret_cast<unsigned *>(side ? Xj : Xi)[(ri * TW_RS + c) / 4] = xw;
                 reinterpret_cast<unsigned *>(side ? Yj : Yi)[(ri * TW_RS + c) / 4] = yw;
