@@ -39,35 +39,34 @@ PEAK_VALU_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 # update (two v_pk_sub_i16, one v_dot2_i32_i16) + admissible minimum (two compares for
 # tabu state and aspiration, one compare and two selects for the running minimum)
 VALU_PER_EVAL = {"tabu": 8, "2opt": 6}
+# block form: the update is on the matrix cores; the select makes a key (one v_lshl_or_b32)
+# and takes two three-way minima a pair of entries (one for 2opt)
+BLOCK_VALU_PER_EVAL = {"tabu": 2, "2opt": 1.5}
 BYTES_PER_EVAL = 8   # an int32 delta read and written per entry per step if kept in HBM
 
 # HBM bytes per launch of the dominant kernel, from rocprofv3 FETCH_SIZE and WRITE_SIZE
 # runs scaled by a plain copy's counts (x2 and x1; see the summaries under profiles/),
 # valid only for the kernel sources they were taken with.
-KERNEL_SOURCES = ["paper_2307_11248_amd/csrc/qap_search.hip", "paper_2307_11248_amd/csrc/qap_internal.h"]
-TRAFFIC = {
-    "c2_n64_dense_tabu": {"bytes": int((2 * 725.5 + 40.0) * 1024), "sources": "c0b7ca82fda47dff"},
-    "c3_n128_euclid_tabu": {"bytes": int((2 * 4415.5 + 144.0) * 1024), "sources": "c0b7ca82fda47dff"},
-    # per dispatch, summed over the kernels of one launch (tiles of 2 rows on 128 and 256
-    # lanes, of 4 rows on 256, 512 and 768)
-    "c4_batched_uneven_tabu": {"bytes": int((2 * (65156.0 + 43345.67 + 8637.87 + 2649.54 + 1970.87)
-                                             + (874.563 + 408.78 + 223.25 + 92.625 + 61.5)) * 1024),
-                               "sources": "c0b7ca82fda47dff"},
-    "n256_dense_tabu": {"bytes": int((2 * 68646900.0 + 67775000.0) * 1024), "sources": "c0b7ca82fda47dff"},
-    "n512_dense_tabu": {"bytes": int((2 * 141803000.0 + 266390000.0) * 1024), "sources": "c0b7ca82fda47dff"},
-}
+KERNEL_SOURCES = ["paper_2307_11248_amd/csrc/" + f for f in
+                  ("qap_search.hip", "qap_block.h", "qap_block_wide.hip", "qap_internal.h")]
+TRAFFIC = {}   # workload: {"bytes": .., "sources": kernel_digest()}; none taken with these sources
 
 
-def roofline(search_evals, kernel_ms, kernel, traffic, ops_per_eval):
-    """HBM roofline of the search phase at 8 B per eval, with the VALU rate beside it."""
+def roofline(search_evals, kernel_ms, kernel, traffic, algo, block):
+    """Roofline of the search phase.  Tiles: HBM at 8 B per eval, with the VALU rate beside it.
+    Block form (the neighbourhood stays in accumulators): VALU, with the HBM-equivalent rate."""
     sec = kernel_ms / 1e3
+    ops = (BLOCK_VALU_PER_EVAL if block else VALU_PER_EVAL)[algo]
     hbm = BYTES_PER_EVAL * search_evals / sec / 1e9
-    valu = ops_per_eval * search_evals / sec / 1e12
-    return {"bound": "hbm", "achieved": round(hbm, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
-            "frac": round(hbm / PEAK_HBM_GBS, 4), "traffic": traffic, "kernel": kernel,
-            "kernel_ms": round(kernel_ms, 4), "bytes_per_eval": BYTES_PER_EVAL, "evals_per_launch": search_evals,
-            "alu_equivalent": {"achieved": round(valu, 3), "peak": round(PEAK_VALU_TOPS, 3), "unit": "TOP/s",
-                               "frac": round(valu / PEAK_VALU_TOPS, 4), "ops_per_eval": ops_per_eval}}
+    valu = ops * search_evals / sec / 1e12
+    of_hbm = {"achieved": round(hbm, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": round(hbm / PEAK_HBM_GBS, 4)}
+    of_alu = {"achieved": round(valu, 3), "peak": round(PEAK_VALU_TOPS, 3), "unit": "TOP/s",
+              "frac": round(valu / PEAK_VALU_TOPS, 4)}
+    rest = {"traffic": traffic, "kernel": kernel, "kernel_ms": round(kernel_ms, 4), "bytes_per_eval": BYTES_PER_EVAL,
+            "evals_per_launch": search_evals}
+    if block:
+        return {"bound": "alu", **of_alu, **rest, "ops_per_eval": ops, "hbm_equivalent": of_hbm}
+    return {"bound": "hbm", **of_hbm, **rest, "alu_equivalent": {**of_alu, "ops_per_eval": ops}}
 
 
 def kernel_digest():
@@ -271,11 +270,12 @@ def run_batch(args, w):
     evals_step = int((ms * (moves + 1)).sum())
     search_evals = int((ms * moves).sum())
     value = evals_step / (ms_step / 1e3)
-    # the search phase: one batch_group_kernel dispatch per tile-shape variant, forked onto
+    # the search phase: one dispatch per block form (or tile-shape variant), forked onto
     # side streams and joined back; the events bracket the fork and the join
-    roof = roofline(search_evals, search_ms, "batch_group_kernel (search phase: %d variant dispatches on the "
-                    "graph's lanes; replay time less the table kernel)" % b.groups(), traffic_for(w.name),
-                    VALU_PER_EVAL["tabu"])
+    roof = roofline(search_evals, search_ms, "%s (search phase: %d variant dispatches on the "
+                    "graph's lanes; replay time less the table kernel)" %
+                    ("batch_group_kernel" if args.tile_rows else "block_kernel", b.groups()), traffic_for(w.name),
+                    "tabu", not args.tile_rows)
     roof["replay_ms"] = round(replay_ms, 4)
     roof["eager_search_ms"] = round(eager_search_ms, 4)
     ns = [I.n for I in insts]
@@ -517,7 +517,9 @@ def main():
     kname = ("search_kernel<%d,%s>" % (rows, "true" if algo == "tabu" else "false") if rows > 0 else
              "stream_kernel<%s,false,%s>" % ("true" if algo == "tabu" else "false",
                                              "true" if n > 256 else "false"))
-    roof = roofline(search_evals, search_ms, kname, traffic_for(w.name), VALU_PER_EVAL[algo])
+    if not args.tile_rows:
+        kname = "wide_block_kernel" if n > 256 else "block_kernel"
+    roof = roofline(search_evals, search_ms, kname, traffic_for(w.name), algo, not args.tile_rows)
 
     out = {"metric": METRIC, "value": value, "unit": "evals/s", "n_gpus": 1, "steps": args.steps,
            "warmup": args.warmup, "ms_per_step": ms_step, "higher_is_better": True, "scaling": "weak",

@@ -70,8 +70,9 @@ const char *qap_strerror(int code);
  * Create a handle for one instance (F, D) of size n (Sec. 2.1) on the current HIP
  * device.  F and D are host pointers, read once and copied; the handle owns its device
  * copies until qap_destroy.  Returns QAP_E_RANGE if an entry lies outside [0, 255].
- * Every entry point serves every n <= QAP_NMAX: the searches hold the neighbourhood in
- * registers and F, F^T, D, D^T in LDS while that fits one workgroup (n <= 176 in the
+ * Every entry point serves every n <= QAP_NMAX.  Searches run in block form where that
+ * serves them (qap_set_tile_rows); the others hold the neighbourhood in register tiles and
+ * G, G^T, D, D^T in LDS while that fits one workgroup (n <= 176 in the
  * batched kernels), and above that run the streamed kernel (neighbourhood in global
  * memory, only G = F[p][p] in LDS).  Above n = 256 they run its wide form, which keeps no
  * G (it reads F and F^T through the permutation), and the neighbourhood table is built by
@@ -251,8 +252,9 @@ int qap_tabu_with_table_async(qap_handle h, int32_t *d_perms, const int32_t *d_t
  * be run any number of times, one run at a time.  It is qap_batch_tables_async (every
  * start's neighbourhood table, Eq. (2), into the plan's scratch) followed by
  * qap_batch_search_async (every search, from those tables); the two halves may be
- * enqueued separately, in that order, on one stream.  The search half runs one kernel
- * per tile-shape variant in use; with more than one, they run on side streams of the
+ * enqueued separately, in that order, on one stream (searches in block form make their
+ * first neighbourhood themselves, in the search half).  The search half runs one kernel
+ * per block form or tile-shape variant in use; with more than one, they run on side streams of the
  * plan forked from and joined back to `stream` by events (one fewer side streams than
  * the hardware queues HIP gives the process, GPU_MAX_HW_QUEUES, unless the environment
  * variable QAP_BATCH_LANES, read by qap_batch_create, sets the count); results do not
@@ -343,8 +345,8 @@ int qap_tabu_batch_concat(const qap_handle *hs, int32_t m, int32_t *perms, const
  * Stepping: each step admits queued requests in arrival order while a slot is free and
  * their footprint fits the pool (a request that does not fit is passed over by later
  * ones that do, for at most 8 steps, after which nothing behind it is admitted first),
- * then runs one chunk of every admitted search in one launch (a second one for searches
- * above n = 256): each search runs until
+ * then runs one chunk of every admitted search, in one launch for each kernel they need
+ * (block form, tiles, frequency memory, above n = 256), side by side: each search runs until
  * about chunk_ms of device time has passed, stopping at an iteration boundary, with its
  * permutation, neighbourhood, tabu list and best solution kept in the pool in between.
  * Searches that finished are then collected and their slot and memory freed.  Every
@@ -432,13 +434,15 @@ int qap_server_destroy(qap_server_handle s);
 int qap_set_tile_rows(qap_handle h, int32_t algo, int32_t rows);
 
 /*
- * Plain tabu searches (no frequency memory) and 2opt up to n = 256 run in block form, not in
- * tiles, unless a shape is set with qap_set_tile_rows (or passed to qap_batch_create): one
- * workgroup per search that holds the neighbourhood as 32 x 32 blocks in matrix-core
- * accumulators.  It takes instances in which the entries of F or of D span at most 127, and
- * tenures with hi - lo < 64 and hi <= 1000; every other search runs in tiles.  Results do not
- * depend on the form.  The functions here report the tile shape a launch would use (the
- * searches of a batch in block form are counted by qap_batch_groups under theirs).
+ * Tabu and 2opt searches run in block form, not in tiles, unless a shape is set with
+ * qap_set_tile_rows (or passed to qap_batch_create): one workgroup per search that holds the
+ * neighbourhood as 32 x 32 blocks in matrix-core accumulators.  Up to n = 256 (single
+ * instances, batches, served requests, and single-instance searches with the frequency memory
+ * with attr 0 or 1 and no step record) it takes instances in which the entries of F or of D
+ * span at most 127, and tenures with hi - lo < 64 and hi <= 1000; above n = 256 single-instance
+ * launches without the frequency memory with hi - lo < 128.  Every other search runs in tiles.
+ * Results do not depend on the form.  The functions here report the tile shape a launch would
+ * use (the searches of a batch in block form are counted by qap_batch_groups under theirs).
  * qap_prefer_tile_rows is qap_set_tile_rows for the searches in tiles only: the block form
  * keeps what it serves.  It is the state qap_tune_tile_rows leaves behind.
  */
