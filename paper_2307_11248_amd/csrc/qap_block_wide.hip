@@ -14,18 +14,21 @@
 //   block's update and select stand between two steps.
 // One iteration (lane t has index u = t in A and C):
 //   B1   the minimum is in sel[it & 1]
-//   A    W_u, the eight side vectors, SD_u; tabu bits and ring (one wave)
+//   A    W_u, the eight side vectors, SD_u; the ring of moves (one wave)
 //   B2
 //   B    blocks: the rows and columns of the move before, moves that become free, the update,
 //        the candidate for it + 1; the matrix products of rows r and s
 //   B3
 //   C    the deltas of rows r and s, their candidate; p; the moves that become free next
+// There are no tabu bits: the waves whose blocks meet rows r and s leave the signs of their
+// slots (32 KB of LDS at n = 512 that hold blocks instead).
 // Bound, up to n = 416, by the reads of the matrices from L2 (4 n^2 bytes an iteration and
-// search, half for symmetric instances), above also by
-// the scratch blocks (0.5 MB an iteration at n = 512, more than L2 holds for 32 searches).
+// search, half for symmetric instances), above also by the scratch blocks (0.4 MB an iteration
+// at n = 512, more than L2 holds for 32 searches: 256 searches moved 285 GB in 55 ms with 64
+// blocks there, 5.2 TB/s; 51 are left).
 // us per iteration with the tiles streamed through scratch (8 bytes a slot, read and written)
-// and here, tables included, 256 searches: n = 300 29.4 and 13.2, n = 512 59.7 and 35.6,
-// n = 512 symmetric 50.1 and 28.3; 64 searches n = 400 30.3 and 19.7; one n = 512 39.4 and 22.6.
+// and here, tables included, 256 searches: n = 300 29.4 and 13.2, n = 512 59.7 and 32.5,
+// n = 512 symmetric 50.1 and 26.2; 64 searches n = 400 30.3 and 19.2; one n = 512 39.4 and 23.0.
 // Registers decide: with 8 blocks above n = 384, or 16 waves of 128 registers and 4 blocks, the
 // kernel spills and takes 43 and 52 us at n = 512.
 #include "qap_block.h"
@@ -54,7 +57,7 @@ __host__ __device__ inline int wb_per_wave(int n) {
 constexpr int WB_LDS = 160 * 1024 - 2048;   // of the workgroup, beside the kernel's own
 
 struct WbPlan {
-    int w, rp, y, vec, perm, fd, bits, ring, blocks, ql, total;   // ql: blocks of a wave in LDS
+    int w, rp, y, vec, perm, fd, ring, blocks, nl, total;   // nl: blocks in LDS
 };
 
 __host__ __device__ inline WbPlan wb_plan(int n, int hi, bool tabu) {
@@ -68,11 +71,10 @@ __host__ __device__ inline WbPlan wb_plan(int n, int hi, bool tabu) {
     q.vec = take(8 * WB_N);
     q.perm = take(np * 4);
     q.fd = take(np * 4);         // f_vv
-    q.bits = take(tabu ? np * nb * 4 : 0);
     q.ring = take(tabu ? blk_ring(hi) * 4 : 0);
-    const int fit = (WB_LDS - o) / (WB_W * 4096), rest = wb_per_wave(n) - wb_regs(wb_groups(n));
-    q.ql = rest <= 0 ? 0 : (fit < rest ? fit : rest);
-    q.blocks = take(q.ql * WB_W * 4096);
+    const int fit = (WB_LDS - o) / 4096, rest = WB_W * (wb_per_wave(n) - wb_regs(wb_groups(n)));
+    q.nl = rest <= 0 ? 0 : (fit < rest ? fit : rest);
+    q.blocks = take(q.nl * 4096);
     q.total = o;
     return q;
 }
@@ -90,6 +92,8 @@ struct WbShared {
     long long sel[2];
     long long red[WB_W];
     int ev[WB_SPAN + 4];    // the number of pairs that become free, then the pairs
+    unsigned tabu[2][WB_N / 32];   // of the pairs of r, and of s, with 32 indices a word
+    int tenure;             // of the move
     int bad;
 };
 
@@ -110,7 +114,6 @@ __global__ void __launch_bounds__(WB_L) __attribute__((amdgpu_waves_per_eu(2, 2)
     int *const rp = reinterpret_cast<int *>(sm + P.rp), *const y = reinterpret_cast<int *>(sm + P.y);
     int8_t *const vec = reinterpret_cast<int8_t *>(sm + P.vec);
     int *const perm = reinterpret_cast<int *>(sm + P.perm), *const fd = reinterpret_cast<int *>(sm + P.fd);
-    unsigned *const bits = reinterpret_cast<unsigned *>(sm + P.bits);
     int *const ring = reinterpret_cast<int *>(sm + P.ring);
     const int32_t *const pin = a.perms_in + (size_t)job * n;
     const int msz = n * rs;                          // bytes of a matrix
@@ -124,10 +127,8 @@ __global__ void __launch_bounds__(WB_L) __attribute__((amdgpu_waves_per_eu(2, 2)
     for (int i = t; i < NP; i += WB_L) rp[i] = -1;
     for (int i = t; i < NP * 8; i += WB_L) reinterpret_cast<int *>(Wv)[i] = 0;
     for (int i = t; i < 8 * WB_N / 4; i += WB_L) reinterpret_cast<int *>(vec)[i] = 0;
-    if (TABU) {
-        for (int i = t; i < NP * NB; i += WB_L) bits[i] = 0;
+    if (TABU)
         for (int i = t; i <= rmask; i += WB_L) ring[i] = -1;
-    }
     if (t < 2) sh.sel[t] = BK_NONE;
     if (t == 0) sh.ev[0] = 0;
     __syncthreads();
@@ -199,9 +200,10 @@ __global__ void __launch_bounds__(WB_L) __attribute__((amdgpu_waves_per_eu(2, 2)
         }
     };
     // the blocks past those in registers: the first of them in LDS, then in scratch
-    const int ql = P.ql;
-    int4 *const near = reinterpret_cast<int4 *>(sm + P.blocks) + wid * ql * 256;
-    int4 *const far = a.tile_work + (size_t)blockIdx.x * a.tile_stride + wid * (per - WB_R - ql) * 256;
+    // (the lower waves take one more where they do not divide)
+    const int qmin = P.nl / WB_W, qmore = P.nl % WB_W, ql = qmin + (wid < qmore ? 1 : 0);
+    int4 *const near = reinterpret_cast<int4 *>(sm + P.blocks) + (wid * qmin + min(wid, qmore)) * 256;
+    int4 *const far = a.tile_work + (size_t)blockIdx.x * a.tile_stride + wid * (per - WB_R - qmin) * 256;
     auto fetch = [&](const int4 *p, v16i &x) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -351,20 +353,19 @@ __global__ void __launch_bounds__(WB_L) __attribute__((amdgpu_waves_per_eu(2, 2)
 
     // ---- the wave that keeps the tabu list
     const bool keeper = TABU && wid == WB_W - 1;
-    int myev[2] = {-1, -1};
     // pairs whose latest tenure ends at iteration x, among moves up to `last`
     auto find_events = [&](int x, int last) {
         int c = 0;
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int tn = lo + lane + 64 * j, i = x - tn;
-            myev[j] = -1;
+            int ev = -1;
             if (tn <= hi && i <= last) {
                 const int e = ring[i & rmask];
-                if ((e >> 18) == tn) myev[j] = e & 0x3ffff;
+                if ((e >> 18) == tn) ev = e & 0x3ffff;
             }
-            const unsigned long long m = __ballot(myev[j] >= 0);
-            if (myev[j] >= 0) sh.ev[1 + c + __builtin_popcountll(m & ((1ull << lane) - 1))] = myev[j];
+            const unsigned long long m = __ballot(ev >= 0);
+            if (ev >= 0) sh.ev[1 + c + __builtin_popcountll(m & ((1ull << lane) - 1))] = ev;
             c += __builtin_popcountll(m);
         }
         if (lane == 0) sh.ev[0] = c;
@@ -407,28 +408,15 @@ __global__ void __launch_bounds__(WB_L) __attribute__((amdgpu_waves_per_eu(2, 2)
         if (improved) bp = pu;
         if (keeper) {
             const int pair = (r << 9) | s, tn = __builtin_amdgcn_readlane(tens, (it - 1) & 63);
-            const unsigned was = bits[r * NB + (s >> 5)];
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-                if (myev[j] >= 0) {
-                    const int x = myev[j] >> 9, z = myev[j] & 511;
-                    atomicAnd(&bits[x * NB + (z >> 5)], ~(1u << (z & 31)));
-                    atomicAnd(&bits[z * NB + (x >> 5)], ~(1u << (x & 31)));
-                }
-            // tabu and not about to expire (made by aspiration): its older entry is void
-            if (((__builtin_amdgcn_readfirstlane((int)was) >> (s & 31)) & 1) &&
-                __ballot(myev[0] == pair || myev[1] == pair) == 0)
+            // only a new best may be tabu (aspiration): the pair's older entry is void
+            if (improved)
                 for (int x = lane; x <= rmask; x += 64) {
                     const int e = ring[x];
                     if (e >= 0 && (e & 0x3ffff) == pair) ring[x] = -1;
                 }
-            if (lane < 2) {
-                if (lane == 0) ring[it & rmask] = (tn << 18) | pair;
-                const int x = lane ? s : r, z = lane ? r : s;
-                if (tn >= 2)   // tabu at it + 1
-                    atomicOr(&bits[x * NB + (z >> 5)], 1u << (z & 31));
-                else
-                    atomicAnd(&bits[x * NB + (z >> 5)], ~(1u << (z & 31)));
+            if (lane == 0) {
+                ring[it & rmask] = (tn << 18) | pair;
+                sh.tenure = tn;
             }
         }
         int dsum = 0, gsum = 0;
@@ -485,11 +473,9 @@ __global__ void __launch_bounds__(WB_L) __attribute__((amdgpu_waves_per_eu(2, 2)
             x[i] = half == ((w >> 2) & 1) ? val : old;
         };
         // rows and columns of blocks that have more to do than the update
-        unsigned hitI = (1u << (r >> 5)) | (1u << (s >> 5)), hitJ = 0;
-        if (it > 1) {
-            hitJ = (1u << (r0 >> 5)) | (1u << (s0 >> 5));
-            hitI |= hitJ;
-        }
+        unsigned hitI = (1u << (r >> 5)) | (1u << (s >> 5));
+        if (it > 1) hitI |= (1u << (r0 >> 5)) | (1u << (s0 >> 5));
+        const unsigned hitJ = hitI;
         if (TABU)
             for (int e = 0; e < nev; ++e) hitI |= 1u << ((e == 0 ? ev0 : __builtin_amdgcn_readfirstlane(sh.ev[1 + e])) >> 14);
         auto repair = [&](v16i &x, int I, int J) __attribute__((always_inline)) {
@@ -526,13 +512,29 @@ __global__ void __launch_bounds__(WB_L) __attribute__((amdgpu_waves_per_eu(2, 2)
                         x[j] = half == ((z >> 2) & 1) && l5 == (w & 31) ? ol2 - 2 * BK_OFF : ol2;
                     }
                 }
-            // rows r and s: out of the minimum until they are recomputed
+            // rows and columns r and s: the tabu state of their slots, for C; rows: out of the
+            // minimum until they are recomputed
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int w = h ? s : r;
+                if (TABU && J == w >> 5 && I != J) {
+                    stay_branch();
+                    unsigned free = 0;   // of the half's rows of the column
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) free |= ((unsigned)x[i] >> 31) << (8 * (i >> 2) + (i & 3));
+                    free = half ? free << 4 : free;
+                    const unsigned both = (unsigned)__builtin_amdgcn_readlane((int)free, w & 31) |
+                                          (unsigned)__builtin_amdgcn_readlane((int)free, 32 + (w & 31));
+                    if (lane == 0) sh.tabu[h][I] = ~both;
+                }
                 if (I != w >> 5) continue;
                 stay_branch();
-                set_row(x, w, BK_NOMOVE - (1 << 20));
+                const int i = ((w >> 3) & 3) * 4 + (w & 3), old = x[i];
+                if (TABU) {
+                    const unsigned long long m = __ballot(old > 0);
+                    if (lane == 0) sh.tabu[h][J] = (unsigned)(((w >> 2) & 1) ? m >> 32 : m);
+                }
+                x[i] = half == ((w >> 2) & 1) ? BK_NOMOVE - (1 << 20) : old;
             }
         };
         auto process = [&](v16i &x, int I, int J) __attribute__((always_inline)) {
@@ -598,8 +600,13 @@ __global__ void __launch_bounds__(WB_L) __attribute__((amdgpu_waves_per_eu(2, 2)
             if (u == s) dr = -dstar;   // the move undone
             if (u == r) ds = -dstar;
             const bool realr = valid && u != r, reals = valid && u != s;
-            const bool tr = TABU && realr && ((bits[r * NB + (u >> 5)] >> (u & 31)) & 1u);
-            const bool ts = TABU && reals && ((bits[s * NB + (u >> 5)] >> (u & 31)) & 1u);
+            bool tr = false, ts = false;
+            if (TABU) {
+                const bool made = sh.tenure >= 2;   // the move itself is tabu at it + 1
+                const unsigned wr = sh.tabu[0][uy >> 5], ws = sh.tabu[1][uy >> 5];
+                tr = realr && (u == s ? made : (wr >> (u & 31)) & 1u);
+                ts = reals && (u == r ? made : (ws >> (u & 31)) & 1u);
+            }
             if (u < NP) {
                 rp[u] = !realr ? BK_NOMOVE : (tr ? dr + BK_OFF : dr - BK_OFF);
                 rp[NP + u] = !reals ? BK_NOMOVE : (ts ? ds + BK_OFF : ds - BK_OFF);
@@ -642,7 +649,7 @@ int wide_block_ok(bool tabu, const SearchArgs &a, size_t max_smem) {
     if (!a.blk || a.freq || a.n <= WIDE_N || a.n > WB_N) return 0;
     if (tabu && (a.hi - a.lo >= WB_SPAN || a.hi > BLOCK_MAX_TENURE)) return 0;
     const WbPlan p = wb_plan(a.n, tabu ? a.hi : 0, tabu);
-    const int spill = wb_per_wave(a.n) - wb_regs(wb_groups(a.n)) - p.ql;   // blocks of a wave in scratch
+    const int spill = wb_per_wave(a.n) - wb_regs(wb_groups(a.n)) - p.nl / WB_W;   // blocks of a wave in scratch
     if (spill > 0 && (long long)spill * WB_W * 256 > a.tile_stride) return 0;
     return (size_t)p.total + 2048 <= max_smem ? 1 : 0;
 }
