@@ -42,30 +42,34 @@ std::vector<int32_t> enumerate_tiles(int n, int rows, int *ninterior) {
 }
 
 int pack_instance(const int32_t *F, const int32_t *D, int n, std::vector<uint8_t> &pack, int *sym, int *blk) {
-    int32_t loF = F[0], hiF = F[0], loD = D[0], hiD = D[0];
-    for (size_t i = 0; i < (size_t)n * n; ++i) {
-        loF = std::min(loF, F[i]); hiF = std::max(hiF, F[i]);
-        loD = std::min(loD, D[i]); hiD = std::max(hiD, D[i]);
-    }
-    if (std::min(loF, loD) < 0 || std::max(hiF, hiD) > 255) return QAP_E_RANGE;
-    bool symF = true, symD = true;
-    for (int i = 0; i < n; ++i)
-        for (int j = 0; j < i; ++j) {
-            if (F[(size_t)i * n + j] != F[(size_t)j * n + i]) symF = false;
-            if (D[(size_t)i * n + j] != D[(size_t)j * n + i]) symD = false;
-        }
-    *sym = (symF && symD) ? 1 : 0;
-    const int spanF = hiF - loF, spanD = hiD - loD;
-    *blk = std::min(spanF, spanD) > 127 ? 0 : (spanF <= spanD ? 1 : 2);
     const int rs = row_stride(n);
-    pack.assign((size_t)4 * n * rs, 0);
-    for (int i = 0; i < n; ++i)
-        for (int j = 0; j < n; ++j) {
-            pack[(size_t)0 * n * rs + (size_t)i * rs + j] = (uint8_t)F[(size_t)i * n + j];
-            pack[(size_t)1 * n * rs + (size_t)i * rs + j] = (uint8_t)F[(size_t)j * n + i];
-            pack[(size_t)2 * n * rs + (size_t)i * rs + j] = (uint8_t)D[(size_t)i * n + j];
-            pack[(size_t)3 * n * rs + (size_t)i * rs + j] = (uint8_t)D[(size_t)j * n + i];
-        }
+    const size_t mat = (size_t)n * rs;
+    pack.assign(4 * mat, 0);
+    int span[2];
+    bool same = true;
+    for (int x = 0; x < 2; ++x) {
+        const int32_t *const src = x ? D : F;
+        uint8_t *const rows = pack.data() + 2 * x * mat, *const cols = rows + mat;
+        int32_t lo = src[0], hi = src[0];
+        for (int i = 0; i < n; ++i)
+            for (int j = 0; j < n; ++j) {
+                const int32_t v = src[(size_t)i * n + j];
+                lo = std::min(lo, v);
+                hi = std::max(hi, v);
+                rows[(size_t)i * rs + j] = (uint8_t)v;
+            }
+        if (lo < 0 || hi > 255) return QAP_E_RANGE;
+        span[x] = hi - lo;
+        // the transpose, in squares that stay in the first-level cache
+        constexpr int B = 64;
+        for (int i0 = 0; i0 < n; i0 += B)
+            for (int j0 = 0; j0 < n; j0 += B)
+                for (int j = j0; j < std::min(j0 + B, n); ++j)
+                    for (int i = i0; i < std::min(i0 + B, n); ++i) cols[(size_t)j * rs + i] = rows[(size_t)i * rs + j];
+        same = same && std::memcmp(rows, cols, mat) == 0;
+    }
+    *sym = same ? 1 : 0;
+    *blk = std::min(span[0], span[1]) > 127 ? 0 : (span[0] <= span[1] ? 1 : 2);
     return QAP_OK;
 }
 
