@@ -856,8 +856,12 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
                     cand = c;
                 } else {
                     // blocks come in order of I, then J: between equal deltas of one row of
-                    // blocks the lower row wins, then (and across them) the earlier block
-                    const bool take = (c | (bI[q] == bI[q - 1] ? 0 : 31)) < cand;
+                    // blocks the lower row wins, then the earlier block, and across them the
+                    // earlier row of blocks (whose row bits move to base, so that it does)
+                    const int m = bI[q] == bI[q - 1] ? 0 : 31;
+                    base += (cand & m) << 9;
+                    cand &= ~m;
+                    const bool take = c < cand;
                     cand = take ? c : cand;
                     base = take ? (bI[q] << 14) | (bJ[q] << 5) : base;
                 }

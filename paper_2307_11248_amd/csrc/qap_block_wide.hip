@@ -240,9 +240,12 @@ __global__ void __launch_bounds__(WB_L) __attribute__((amdgpu_waves_per_eu(2, 2)
         c |= half << 2;
         const int v = J * 32 + l5;
         c = v == er || v == es ? INT32_MAX : c;
-        // between equal deltas of one row of blocks the lower row wins, then (and across them)
-        // the earlier block
-        const bool take = (c | (I == pI ? 0 : 31)) < cand;
+        // between equal deltas of one row of blocks the lower row wins, then the earlier block,
+        // and across them the earlier row of blocks (whose row bits move to base)
+        const int m = I == pI ? 0 : 31;
+        base += (cand & m) << 9;
+        cand &= ~m;
+        const bool take = c < cand;
         cand = take ? c : cand;
         base = take ? (I << 14) | (J << 5) : base;
         pI = I;

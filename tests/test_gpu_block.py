@@ -272,3 +272,41 @@ def test_wide_block_sizes(n, lohi, sym):
         p, c, st = h.two_opt(perms, max_iters=60)
     for j, r in enumerate(pmap(lambda q: oracle.two_opt(F, D, q, max_iters=60), list(perms))):
         assert (p[j] == r[0]).all() and c[j] == r[1] and st[j] == r[2], j
+
+
+@pytest.mark.parametrize("n", [64, 255, 256, 257, 511, 512])
+@pytest.mark.parametrize("sym", [False, True])
+def test_block_extreme_deltas(n, sym):
+    """Whole rows (and columns) at the ends of the spans: the largest deltas there are."""
+    note("block extreme deltas n=%d sym=%d" % (n, sym))
+    rng = np.random.default_rng([n, sym])
+    a, b = np.arange(n) % 2, (np.arange(n) // 2) % 2
+    F, D = a[:, None] + 0 * a[None, :], b[:, None] + 0 * b[None, :]
+    if sym:
+        F, D = np.maximum(F, F.T), np.maximum(D, D.T)
+    F, D = (255 * F).astype(np.int32), (127 * D).astype(np.int32)
+    perms = W.starts(rng, n, 2)
+    perms[1] = np.argsort(a[np.argsort(b, kind="stable")], kind="stable")
+    lo, hi = W.paper_tenure_range(n)
+    hi = min(hi, lo + 60)
+    with qap.Handle(F, D) as h:
+        check_tabu(F, D, perms, 150, lo, hi, 8, h.tabu(perms, 150, lo, hi, 8))
+        p, c, st = h.two_opt(perms, max_iters=40)
+    for j, r in enumerate(pmap(lambda q: oracle.two_opt(F, D, q, max_iters=40), list(perms))):
+        assert (p[j] == r[0]).all() and c[j] == r[1] and st[j] == r[2], j
+
+
+# most deltas tie: the lowest pair wins across the blocks of a lane, of a wave and of the waves
+@pytest.mark.parametrize("n", [40, 100, 150, 165, 190, 210, 224, 240, 256, 270, 330, 400, 512])
+@pytest.mark.parametrize("sym", [False, True])
+def test_block_ties(n, sym):
+    note("block ties n=%d sym=%d" % (n, sym))
+    F, D, rng = instance(n, sym, False, 1, 1)
+    F = F * (rng.random((n, n)) < 0.1)
+    F = (np.maximum(F, F.T) if sym else F).astype(np.int32)
+    D = (np.add.outer(np.arange(n) % 2, np.arange(n) % 2)).astype(np.int32)
+    perms = W.starts(rng, n, 3)
+    lo, hi = W.paper_tenure_range(n)
+    hi = min(hi, lo + 60)
+    with qap.Handle(F, D) as h:
+        check_tabu(F, D, perms, 400, lo, hi, 8, h.tabu(perms, 400, lo, hi, 8))
