@@ -438,7 +438,7 @@ int qap_set_tile_rows(qap_handle h, int32_t algo, int32_t rows);
  * qap_set_tile_rows (or passed to qap_batch_create): one workgroup per search that holds the
  * neighbourhood as 32 x 32 blocks in matrix-core accumulators.  Up to n = 256 (single
  * instances, batches, served requests, and single-instance searches with the frequency memory
- * with attr 0 or 1 and no step record) it takes instances in which the entries of F or of D
+ * with attr 0 or 1, div 0 and no step record) it takes instances in which the entries of F or of D
  * span at most 127, and tenures with hi - lo < 64 and hi <= 1000; above n = 256 single-instance
  * launches without the frequency memory with hi - lo < 128.  Every other search runs in tiles.
  * Results do not depend on the form.  The functions here report the tile shape a launch would

@@ -209,10 +209,10 @@ int launch_shape(qap_ctx *h, int algo, int k) {
 // Whether a tabu (algo 0, 2) or 2opt (1) search of this instance runs in block form: no
 // tile shape is set, and the block form serves it (it is faster than every tile shape at
 // every n it serves: 1.6 to 5.6 times over n = 12 .. 256, one search or 4096 at a time).
-// Searches with the frequency memory do so for pairs and marked units (attr 0, 1) without a
-// step record.
-bool use_block(const qap_ctx *h, int algo, int lo, int hi, bool freq = false, int attr = 0, bool trace = false) {
-    if (freq && (attr > 1 || trace)) return false;
+// Searches with the frequency memory do so for pairs and marked units (attr 0, 1) without the
+// diversification move and without a step record.
+bool use_block(const qap_ctx *h, int algo, int lo, int hi, bool freq = false, int attr = 0, bool more = false) {
+    if (freq && (attr > 1 || more)) return false;
     return h->block_on[algo] && block_ok(h->n, h->sym, h->blk, algo != 1, lo, hi, h->max_smem);
 }
 
@@ -290,7 +290,7 @@ hipError_t launch_searches(qap_ctx *h, int algo, int32_t *d_perms, const int32_t
     a.trace = d_trace;
     a.trace_cap = trace_cap;
     hipError_t e = hipSuccess;
-    if (use_block(h, algo, lo, hi, d_freq != nullptr, attr, d_trace != nullptr)) {
+    if (use_block(h, algo, lo, hi, d_freq != nullptr, attr, div > 0 || d_trace)) {
         const size_t smem = block_smem_bytes(h->n, h->sym, hi, algo == 0);
         for (int j = 0; j < (plain ? k : 1) && e == hipSuccess; ++j) {
             a.job0 = j;
@@ -365,7 +365,7 @@ int run_search(qap_ctx *h, int algo, int32_t *d_perms, int k, int iters, int lo,
     if (h->rows_choice[algo] < 0) return QAP_E_UNSUPPORTED;
     if (k == 0) return QAP_OK;
     int32_t *d_table = nullptr;
-    if (use_block(h, algo, lo, hi, d_freq != nullptr, attr, d_trace != nullptr))   // makes its first neighbourhood itself
+    if (use_block(h, algo, lo, hi, d_freq != nullptr, attr, div > 0 || d_trace))   // makes its first neighbourhood itself
         return dev_err(launch_searches(h, algo, d_perms, nullptr, k, iters, lo, hi, seed, start_base, d_cost, d_steps,
                                        st, plain, d_freq, div, attr));
     int rc = make_tables(h, d_perms, k, &d_table, st);

@@ -198,16 +198,13 @@ __device__ inline void sel_min(long long *slot, int d, int key) {
 // them once).
 struct BlkShared {
     long long sel[2];      // the minimum over the waves, by iteration parity
-    long long dsel;        // diversification: the lowest (count, key)
-    int ddelta;            // and its delta
-    int pad;
     long long red[8];
     int ev[68];            // the number of pairs that become free, then the pairs
     int bad, chunk_end;
 };
 
-// FREQ: tabu that keeps the frequency memory (a.freq), with the diversification move (a.div)
-// and, for a.attr 1, marked units in place of tabu pairs.
+// FREQ: tabu that keeps the frequency memory (a.freq), for a.attr 1 with marked units in place
+// of tabu pairs.
 template <int NB, bool SYM, bool TABU, bool RESUME, bool BUSY, bool FREQ>
 __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigned char *sm, BlkShared &sh) {
     static_assert((TABU || !RESUME) && (!FREQ || (TABU && !RESUME && !BUSY)), "forms in use");
@@ -268,7 +265,6 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
         for (int i = t; i < 4 * 64 * KS / 4; i += L) reinterpret_cast<int *>(side)[i] = 0;
     if (t < 2) sel[t] = BK_NONE;
     if (FREQ) {
-        if (t == 0) sh.dsel = BK_NONE;
         if (t == 0) s_ev[0] = 0;
         for (int i = t; i < a.m; i += L) a.freq[i] = 0;
         vm_done();   // before the adds of the housekeeping wave
@@ -379,29 +375,11 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
     // chunk) ends here
     int r = 0, s = 0, dstar = 0;
     bool improved = false, stopped = false;
-    int last_imp = 0;   // FREQ: the iteration of the last new best or diversification
-    // scan, publish (FREQ, block waves): the lowest (count, key) of the wave's free slots into
-    // sh.dsel; the delta of the pair `key`, if the wave holds it, into sh.ddelta
-    auto next_move_from = [&](auto scan, auto publish) -> bool {
+    auto next_move = [&]() -> bool {
         const long long mk = sel[it & 1];
         if (RESUME && __builtin_amdgcn_readfirstlane(s_chunk_end)) return false;
         dstar = __builtin_amdgcn_readfirstlane((int)(mk >> 32));
-        int key = __builtin_amdgcn_readfirstlane((int)mk);
-        bool diversified = false;
-        if (FREQ && a.div > 0 && it - last_imp > a.div) {
-            // the free pair exchanged least often so far, the lowest key among equals
-            scan();
-            __syncthreads();
-            const long long best2 = sh.dsel;
-            if (__builtin_amdgcn_readfirstlane((int)(best2 >> 32)) != INT32_MAX) {   // else every move is tabu
-                key = __builtin_amdgcn_readfirstlane((int)best2);
-                publish(key);
-                __syncthreads();
-                dstar = __builtin_amdgcn_readfirstlane(sh.ddelta);
-                diversified = true;
-                if (wid == TW && lane == 0) sh.dsel = BK_NONE;   // (read by all before the barrier)
-            }
-        }
+        const int key = __builtin_amdgcn_readfirstlane((int)mk);
         if (TABU ? dstar == INT32_MAX : dstar >= 0) {
             stopped = true;
             return false;
@@ -411,10 +389,8 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
         gap += dstar;
         improved = TABU && gap < 0;
         if (improved) gap = 0;
-        if (FREQ && (improved || diversified)) last_imp = it;
         return true;
     };
-    auto next_move = [&]() -> bool { return next_move_from([] {}, [](int) {}); };
     // aspiration threshold of the next select: a tabu move is allowed below it
     auto aspire = [&]() -> int { return max(-gap, -(1 << 24)); };
 
@@ -666,7 +642,6 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
             // chunk end: decided every 16 iterations, read by every wave after B1
             if (RESUME && clock_end != 0 && it != it_first && (it & 15) == 0 && lane == 0)
                 s_chunk_end = (long long)wall_clock64() >= clock_end;
-            if (FREQ && a.div > 0) vm_done();   // the move before is counted
             __syncthreads();   // B1
             if (!next_move()) break;
             cur += dstar;
@@ -936,45 +911,7 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
                 }
             v4i ev = {0, 0, 0, 0};
             if (TABU) ev = *reinterpret_cast<const v4i *>(s_ev);
-            const auto scan = [&] {
-                patch();                 // nothing stale may be chosen
-                r0 = s0 = NOWHERE;
-                long long low = BK_NONE;
-#pragma unroll
-                for (int q = 0; q < BPW; ++q) {
-                    if (!has(q)) break;
-                    const int v = bJ[q] * 32 + l5;
-#pragma unroll 1
-                    for (int i = 0; i < 16; ++i) {
-                        const int x = bI[q] * 32 + 8 * (i >> 2) + 4 * half + (i & 3), val = acc[q][i];
-                        // (free slots are moves; a mirror slot loses to its pair's own)
-                        if (val < 0 && !(marks && (mark[x] > it || mark[v] > it))) {
-                            const int cnt = __hip_atomic_load(a.freq + pidx(n, min(x, v), max(x, v)), __ATOMIC_RELAXED,
-                                                              __HIP_MEMORY_SCOPE_AGENT);
-                            const long long c = ((long long)cnt << 32) | (unsigned)((x << 9) | v);
-                            low = c < low ? c : low;
-                        }
-                    }
-                }
-                if (low != BK_NONE) sel_min(&sh.dsel, (int)(low >> 32), (int)low);
-            };
-            const auto publish = [&](int key) {
-                const int x = key >> 9, y = key & 511;
-                const unsigned me = in_row(x) & in_col(y);
-#pragma unroll
-                for (int q = 0; q < BPW; ++q)
-                    if (has(q) && ((me >> q) & 1)) {
-                        stay_branch();
-                        const int i = ((x >> 3) & 3) * 4 + (x & 3), val = acc[q][i];
-                        if (half == ((x >> 2) & 1) && l5 == (y & 31)) sh.ddelta = val + BK_OFF;
-                    }
-            };
-            bool go;
-            if constexpr (FREQ)
-                go = next_move_from(scan, publish);
-            else
-                go = next_move();
-            if (!go) break;
+            if (!next_move()) break;
             const int thr = aspire();
             // ---- A
             patch();
@@ -1107,7 +1044,6 @@ block_kernel(SearchArgs a, BatchArgs b) {
         if (FREQ) {
             it.m = a.m;
             it.freq = a.freq + (size_t)job * a.m;
-            it.div = a.div;
             it.attr = a.attr;
         }
     }

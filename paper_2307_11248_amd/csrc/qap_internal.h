@@ -323,7 +323,7 @@ size_t block_ring_bytes(int hi);
 int block_ok(int n, int sym, int blk, bool tabu, int lo, int hi, size_t max_smem);
 // One search per block: of one instance (a), or items of one form of a batch (b); busy: the
 // searches in flight outnumber the compute units.  a->freq: tabu with the frequency memory
-// (attr 0 or 1, no step record).
+// (attr 0 or 1, no diversification move, no step record).
 hipError_t launch_block(bool tabu, int form, bool busy, size_t smem, const SearchArgs *a, const BatchArgs *b, int grid,
                         hipStream_t st);
 // Block form above WIDE_N (n to 512), for launches of searches with their tables and the
