@@ -183,6 +183,17 @@ struct Tenures {
 // it and selecting (the sixteen slots of a block each time).
 __device__ inline void stay_branch() { asm volatile(""); }
 
+// A barrier behind the wave's own LDS operations (lgkmcnt 0).  __syncthreads alone asks for that
+// wait in a form that the compiler may take out where nothing is in flight, and it takes it out of
+// the head of a loop whose entry has nothing in flight though the loop's own end has: waves then
+// passed B1 with the minimum, the recomputed deltas or the expiring moves of others still on their
+// way to LDS.  This one stays.
+__device__ inline void block_sync() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    __syncthreads();
+}
+
 // waits for the wave's own global stores and atomics (vmcnt 0)
 __device__ inline void vm_done() { __builtin_amdgcn_s_waitcnt(0x0f70); }
 
@@ -269,7 +280,7 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
         for (int i = t; i < a.m; i += L) a.freq[i] = 0;
         vm_done();   // before the adds of the housekeeping wave
     }
-    __syncthreads();
+    block_sync();
     const int32_t *const pin = resume ? a.st_perm : a.perm_in;
     for (int u = t; u < n; u += L) {
         const int v = pin[u];
@@ -277,7 +288,7 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
         bestp[u] = resume ? a.st_bestp[u] : v;
         if (v < 0 || v >= n || atomicExch(&rp[v], u) != -1) s_bad = 1;
     }
-    __syncthreads();
+    block_sync();
     if (s_bad) {
         if (a.perm_out != a.perm_in)
             for (int u = t; u < n; u += L) a.perm_out[u] = pin[u];
@@ -321,7 +332,7 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
             *reinterpret_cast<unsigned *>(G + at(row, c0)) = wg;
         }
     }
-    __syncthreads();
+    block_sync();
 
     // ---- task waves: SD_u of their indices (both halves of the wave hold it); cost (Eq. 1)
     const bool task = wid < TW;
@@ -356,7 +367,7 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
     }
     int it = resume ? __builtin_amdgcn_readfirstlane(st->it) : 1;   // tabu: the iteration; 2opt: moves made + 1
     const int it_first = it;
-    __syncthreads();
+    block_sync();
     long long cur = 0;
 #pragma unroll
     for (int w = 0; w < TW; ++w) cur += s_red[w];
@@ -426,7 +437,7 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
         int8_t *const sideM = side + half * 2 * 64 * KS;
         const int8_t *const sideA = side + (side_s ? 64 * KS : 0) + chunk;
         while (it <= cap) {
-            __syncthreads();   // B1
+            block_sync();   // B1
             if (!next_move()) break;
             const int thr = aspire();
             // ---- A
@@ -493,7 +504,7 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
                 dsum[c] = (half ? dsm >> 16 : (int)(short)dsm) - duu[c] - dbb;   // d_ub + d_bu - d_uu - d_bb
                 gsum[c] = half ? (int)(short)gsm : gsm >> 16;                    // g_ub + g_bu under p'
             }
-            __syncthreads();   // B2
+            block_sync();   // B2
             // ---- B: C[b][u] = T'_ub + T'_bu, and SD'_r, SD'_s
             const int gbb = G[at(b, b)];
             int guu[TC];
@@ -642,7 +653,7 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
             // chunk end: decided every 16 iterations, read by every wave after B1
             if (RESUME && clock_end != 0 && it != it_first && (it & 15) == 0 && lane == 0)
                 s_chunk_end = (long long)wall_clock64() >= clock_end;
-            __syncthreads();   // B1
+            block_sync();   // B1
             if (!next_move()) break;
             cur += dstar;
             // ---- A
@@ -686,7 +697,7 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
                         atomicAnd(&bits[x * NB + (y >> 5)], ~(1u << (y & 31)));
                 }
             }
-            __syncthreads();   // B2
+            block_sync();   // B2
             // ---- B
             if (lane == 0) {
                 const int x = perm[r], y = perm[s];
@@ -901,7 +912,7 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
         };
         candidates(-1, -1, it, aspire());
         while (it <= cap) {
-            __syncthreads();   // B1
+            block_sync();   // B1
             // what A needs beside the move, read together with it
 #pragma unroll
             for (int q = 0; q < BPW; ++q)
@@ -952,7 +963,7 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
                         set_row(q, x, BK_NOMOVE - (1 << 20));
                     }
             }
-            __syncthreads();   // B2
+            block_sync();   // B2
             // ---- B (its few reads go before the task waves' many)
             __builtin_amdgcn_s_setprio(3);
 #pragma unroll
@@ -984,7 +995,7 @@ __device__ __attribute__((always_inline)) void block_body(const Item &a, unsigne
     }
 
     // ---- results
-    __syncthreads();
+    block_sync();
     const bool finished = !RESUME || stopped || it > cap;
     if (RESUME) {
         for (int x = t; x < n; x += L) {

@@ -131,11 +131,11 @@ __global__ void __launch_bounds__(WB_L) __attribute__((amdgpu_waves_per_eu(2, 2)
         for (int i = t; i <= rmask; i += WB_L) ring[i] = -1;
     if (t < 2) sh.sel[t] = BK_NONE;
     if (t == 0) sh.ev[0] = 0;
-    __syncthreads();
+    block_sync();
     int pu = valid ? pin[u] : 0;
     if (u < NP) perm[u] = pu;
     if (valid && (pu < 0 || pu >= n || atomicExch(&rp[pu], u) != -1)) sh.bad = 1;
-    __syncthreads();
+    block_sync();
     if (sh.bad) {
         int32_t *const out = a.perm_out + (size_t)job * n;
         if (out != pin && valid) out[u] = pu;
@@ -175,7 +175,7 @@ __global__ void __launch_bounds__(WB_L) __attribute__((amdgpu_waves_per_eu(2, 2)
     }
     part += __shfl_xor(part, 32, 64);
     if (lane == 0) sh.red[wid] = part;
-    __syncthreads();
+    block_sync();
     long long cur = 0;
 #pragma unroll
     for (int w = 0; w < WB_W; ++w) cur += sh.red[w];
@@ -394,7 +394,7 @@ __global__ void __launch_bounds__(WB_L) __attribute__((amdgpu_waves_per_eu(2, 2)
         half = lane >> 5, l5 = lane & 31, chunk = (lane >> 4) * 16, crow = lane & 15;
         u = wid * 64 + lane;
         valid = u < n;
-        __syncthreads();   // B1
+        block_sync();   // B1
         const long long mk = sh.sel[it & 1];
         const int dstar = __builtin_amdgcn_readfirstlane((int)(mk >> 32));
         const int key = __builtin_amdgcn_readfirstlane((int)mk);
@@ -465,7 +465,7 @@ __global__ void __launch_bounds__(WB_L) __attribute__((amdgpu_waves_per_eu(2, 2)
                 }
             }
         }
-        __syncthreads();   // B2
+        block_sync();   // B2
         // ---- B
         um = uk = 0;
         const int thrk = (thr - BK_OFF) * 32;
@@ -588,7 +588,7 @@ __global__ void __launch_bounds__(WB_L) __attribute__((amdgpu_waves_per_eu(2, 2)
             while (um != M) one_step();
         }
         publish(it + 1);
-        __syncthreads();   // B3
+        block_sync();   // B3
         // ---- C
         if (active) {
             const int uy = min(u, NP - 1);
