@@ -331,6 +331,16 @@ int plan_request(qap_server *s, Request *r, int n, int lo, int hi) {
     return QAP_OK;
 }
 
+// A step that failed part way: what it has enqueued still uses the requests' regions, the item
+// and state arrays and their host copies, and may not be joined to the server's stream, so it is
+// waited for on every stream before the step returns.
+int step_failed(qap_server *s, hipError_t e) {
+    for (hipStream_t st : s->side)
+        if (st) (void)hipStreamSynchronize(st);
+    (void)hipStreamSynchronize(s->st);
+    return dev_err_at(e, "step_locked");
+}
+
 // One step: admit, run one chunk of every admitted search, collect the finished ones.
 // Called with s->step_mu held; takes s->mu only around the shared state.
 int step_locked(qap_server *s, int32_t *active_out, int32_t *pending_out) {
@@ -475,7 +485,7 @@ int step_locked(qap_server *s, int32_t *active_out, int32_t *pending_out) {
             e = hipMemcpyAsync(s->h_moves, s->d_moves, (size_t)s->max_active * 4, hipMemcpyDeviceToHost, s->st);
         if (e == hipSuccess) e = hipStreamSynchronize(s->st);
     }
-    if (e != hipSuccess) return dev_err(e);
+    if (e != hipSuccess) return step_failed(s, e);
     // finished searches: their best permutations come back before they are published
     std::vector<Request *> fin;
     std::vector<std::vector<int32_t>> perms;
@@ -501,7 +511,7 @@ int step_locked(qap_server *s, int32_t *active_out, int32_t *pending_out) {
         }
     }
     if (e == hipSuccess && !fin.empty()) e = hipStreamSynchronize(s->st);
-    if (e != hipSuccess) return dev_err(e);
+    if (e != hipSuccess) return step_failed(s, e);
     const double t = now_ms();
     std::lock_guard<std::mutex> lk(s->mu);
     std::vector<Request *> keep;
