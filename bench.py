@@ -272,7 +272,7 @@ def run_batch(args, w):
     value = evals_step / (ms_step / 1e3)
     # the search phase: one dispatch per block form (or tile-shape variant), forked onto
     # side streams and joined back; the events bracket the fork and the join
-    roof = roofline(search_evals, search_ms, "%s (search phase: %d variant dispatches on the "
+    roof = roofline(search_evals, search_ms, "%s (search phase: %d kernel dispatches on the "
                     "graph's lanes; replay time less the table kernel)" %
                     ("batch_group_kernel" if args.tile_rows else "block_kernel", b.groups()), traffic_for(w.name),
                     "tabu", not args.tile_rows)

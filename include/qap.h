@@ -299,11 +299,13 @@ int qap_batch_create_freq(const qap_handle *hs, int32_t m, const int32_t *k_per,
                           qap_batch_handle *out);
 int qap_batch_freq_async(qap_batch_handle b, int32_t *d_freq, void *stream);
 int qap_batch_size(qap_batch_handle b, int64_t *starts_out, int64_t *perm_ints_out);
-/* Kernel dispatches of one qap_batch_search_async: returns the number of tile-shape
- * variants the plan uses (one dispatch each, forked onto side streams of `stream` and
- * joined back), and, when count_out (int32[9]) is not NULL, the searches per variant in
- * the order: tiles of 2, 4, 8 rows on 512 lanes, streamed, 2 rows on 128 and on 256
- * lanes, 4 rows on 256 and on 768 lanes, the wide streamed form (n above 256). */
+/* Kernel dispatches of one qap_batch_search_async: returns the number of kernels the plan
+ * uses, one per tile-shape variant and one per block form in use (ceil(n / 32), symmetric or
+ * not), one dispatch each, forked onto side streams of `stream` and joined back; and, when
+ * count_out (int32[9]) is not NULL, the searches per tile-shape variant in the order: tiles of
+ * 2, 4, 8 rows on 512 lanes, streamed, 2 rows on 128 and on 256 lanes, 4 rows on 256 and on
+ * 768 lanes, the wide streamed form (n above 256).  The plan's other searches (qap_batch_size)
+ * run in block form. */
 int qap_batch_groups(qap_batch_handle b, int32_t *count_out);
 int qap_batch_run_async(qap_batch_handle b, int32_t *d_perms, int64_t *d_best, int32_t *d_done,
                         void *stream);
@@ -441,8 +443,8 @@ int qap_set_tile_rows(qap_handle h, int32_t algo, int32_t rows);
  * with attr 0 or 1, div 0 and no step record) it takes instances in which the entries of F or of D
  * span at most 127, and tenures with hi - lo < 64 and hi <= 1000; above n = 256 single-instance
  * launches without the frequency memory with hi - lo < 128.  Every other search runs in tiles.
- * Results do not depend on the form.  The functions here report the tile shape a launch would
- * use (the searches of a batch in block form are counted by qap_batch_groups under theirs).
+ * Results do not depend on the form.  qap_get_tile_rows and qap_launch_tile_rows report the
+ * tile shape of the searches that run in tiles.
  * qap_prefer_tile_rows is qap_set_tile_rows for the searches in tiles only: the block form
  * keeps what it serves.  It is the state qap_tune_tile_rows leaves behind.
  */

@@ -455,7 +455,6 @@ struct qap_batch {
     size_t group_smem[GV_COUNT] = {};
     bool busy = false;              // more searches than compute units
     int narrow = 0;                 // items of the tile shapes up to WIDE_N (they come first)
-    int tile_count[BV_COUNT] = {};  // searches per tile shape, reported by qap_batch_groups
     // The groups run on `nlanes` side streams forked from the caller's stream, the groups
     // of one lane back to back: lane_groups[lane_begin[l] .. lane_begin[l + 1]).  Streams
     // beyond the device's hardware queues would share queues, and kernels on one queue
@@ -1035,7 +1034,6 @@ int batch_create_impl(const qap_handle *hs, int32_t m, const int32_t *k_per, int
         if (v < 0) continue;   // (not reached: batch_fits and batch_freq_fits turn such shapes away)
         b->group_begin[v] = i;
         ++b->group_count[v];
-        ++b->tile_count[tile_variant(items[i])];
         b->narrow += v < BV_WIDE;
     }
     int ngroups = 0;
@@ -1154,18 +1152,18 @@ extern "C" int qap_batch_groups(qap_batch_handle b, int32_t *count_out) {
         if (count_out) {
             for (int v = 0; v < BV_COUNT; ++v) count_out[v] = 0;
             for (int v = 0; v < BV_COUNT; ++v) {
-                if (!b->tile_count[v]) continue;
+                if (!b->group_count[v]) continue;
                 const int rows = v == BV_R4 || v == BV_R4_256 || v == BV_R4_768 ? 4 : (v == BV_R8 ? 8 : 2);
                 count_out[v == BV_STREAM ? BV_STREAM : (rows == 2 ? BV_R2 : (rows == 4 ? BV_R4 : BV_R8))] +=
-                    b->tile_count[v];
+                    b->group_count[v];
             }
         }
         return b->count > 0 ? 1 : 0;
     }
     int groups = 0;
-    for (int v = 0; v < BV_COUNT; ++v) {
-        if (count_out) count_out[v] = b->tile_count[v];
-        groups += b->tile_count[v] > 0;
+    for (int v = 0; v < GV_COUNT; ++v) {
+        if (count_out && v < BV_COUNT) count_out[v] = b->group_count[v];
+        groups += b->group_count[v] > 0;
     }
     return groups;
 }

@@ -406,8 +406,9 @@ class Batch:
                                          _dptr(d_done, "int32"), _stream_ptr(stream)), "qap_batch_run_async")
 
     def groups(self, counts: bool = False):
-        """Kernel dispatches of one search phase (one per tile-shape variant in use); with
-        counts=True also the searches per variant (int32[9], the header's order)."""
+        """Kernel dispatches of one search phase (one per tile-shape variant and block form in
+        use); with counts=True also the searches per tile-shape variant (int32[9], the header's
+        order; the plan's other searches run in block form)."""
         c = np.zeros(9, dtype=np.int32)
         g = _check(lib().qap_batch_groups(self._b, _ptr(c, _i32p)), "qap_batch_groups")
         return (g, c) if counts else g
