@@ -8,12 +8,15 @@ The default workload is the uneven batch (--workload c4: 512 instances, n from 2
 150, 8 starts each, 5000 tabu iterations): every start of every instance runs in one
 launch of the batched kernels, and the step is a captured HIP graph (reset, tables,
 searches) replayed once per step.  Other workloads: c1, c2, c3-2opt, c3-tabu (single
-instances), c5 (the serving stream), stream (n = 256, the streamed kernel), wide (n = 512,
-the wide streamed kernel).
+instances), c5 (the serving stream), stream (n = 256), wide (n = 512).
 
-The roofline is priced in HBM bytes: a swap-delta eval (one neighbourhood entry made
-current for one step of one search) is an int32 read and write, 8 bytes, against the
-8 TB/s of MI355X's HBM3E; the VALU rate of the same evals is reported beside it.
+The unit of work is a swap-delta eval: one neighbourhood entry made current for one step of
+one search.  For searches in tiles the roofline is priced in HBM bytes, an int32 read and
+write per eval, against the 8 TB/s of MI355X's HBM3E, with the VALU rate beside it.  For
+searches in block form, which keep the neighbourhood in accumulators, it is priced in the
+VALU instructions of the select alone (the update runs on the matrix cores, and the rows
+recomputed each step are not counted), with the HBM rate of the tiles' pricing beside it;
+a fraction of either is a rate of evals, not a share of what the kernel executes.
 
 Prints one JSON line (see the keys below).  --gpus N with N > 1 is refused: this build
 runs on one GPU.
@@ -48,15 +51,19 @@ BYTES_PER_EVAL = 8   # an int32 delta read and written per entry per step if kep
 # runs scaled by a plain copy's counts (x2 and x1; see the summaries under profiles/),
 # valid only for the kernel sources they were taken with.
 KERNEL_SOURCES = ["paper_2307_11248_amd/csrc/" + f for f in
-                  ("qap_search.hip", "qap_block.h", "qap_block_wide.hip", "qap_internal.h")]
+                  ("qap_search.hip", "qap_block.h", "qap_block.hip", "qap_block_busy.hip", "qap_block_freq.hip",
+                   "qap_block_wide.hip", "qap_internal.h")]
 TRAFFIC = {}   # workload: {"bytes": .., "sources": kernel_digest()}; none taken with these sources
 
 
-def roofline(search_evals, kernel_ms, kernel, traffic, algo, block):
+def roofline(search_evals, kernel_ms, kernel, traffic, algo, block_evals):
     """Roofline of the search phase.  Tiles: HBM at 8 B per eval, with the VALU rate beside it.
-    Block form (the neighbourhood stays in accumulators): VALU, with the HBM-equivalent rate."""
+    Block form (the neighbourhood stays in accumulators), where all evals are of it: VALU, with
+    the HBM-equivalent rate."""
     sec = kernel_ms / 1e3
-    ops = (BLOCK_VALU_PER_EVAL if block else VALU_PER_EVAL)[algo]
+    block = block_evals == search_evals
+    share = block_evals / search_evals if search_evals else 0.0
+    ops = round(BLOCK_VALU_PER_EVAL[algo] * share + VALU_PER_EVAL[algo] * (1 - share), 4)
     hbm = BYTES_PER_EVAL * search_evals / sec / 1e9
     valu = ops * search_evals / sec / 1e12
     of_hbm = {"achieved": round(hbm, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": round(hbm / PEAK_HBM_GBS, 4)}
@@ -197,7 +204,10 @@ def run_batch(args, w):
         from paper_2307_11248_amd.autotune import TileCache
         t0 = time.perf_counter()
         cache = TileCache(args.tune_cache)
-        rows = cache.apply_all(hs, "batch")
+        rows = ["block"] * m               # (a search in block form has no tile shape to tune)
+        tiled = [t for t in range(m) if not hs[t].block_form("batch", lo[t], hi[t])]
+        for t, r in zip(tiled, cache.apply_all([hs[t] for t in tiled], "batch")):
+            rows[t] = r
         cache.save()
         tune_s = time.perf_counter() - t0
         if args.tile_rows:
@@ -270,12 +280,16 @@ def run_batch(args, w):
     evals_step = int((ms * (moves + 1)).sum())
     search_evals = int((ms * moves).sum())
     value = evals_step / (ms_step / 1e3)
-    # the search phase: one dispatch per block form (or tile-shape variant), forked onto
+    # the search phase: one dispatch per block form and tile-shape variant, forked onto
     # side streams and joined back; the events bracket the fork and the join
+    in_block = [h.block_form("batch", lo[t], hi[t]) for t, h in enumerate(hs)]
+    block_evals = int((ms * moves)[np.repeat(in_block, k)].sum())
+    ngroups, tile_searches = b.groups(counts=True)
+    assert b.starts - int(tile_searches.sum()) == k * sum(in_block)
     roof = roofline(search_evals, search_ms, "%s (search phase: %d kernel dispatches on the "
                     "graph's lanes; replay time less the table kernel)" %
-                    ("batch_group_kernel" if args.tile_rows else "block_kernel", b.groups()), traffic_for(w.name),
-                    "tabu", not args.tile_rows)
+                    (" and ".join(["block_kernel"] * any(in_block) + ["batch_group_kernel"] * (not all(in_block))),
+                     ngroups), traffic_for(w.name), "tabu", block_evals)
     roof["replay_ms"] = round(replay_ms, 4)
     roof["eager_search_ms"] = round(eager_search_ms, 4)
     ns = [I.n for I in insts]
@@ -285,9 +299,10 @@ def run_batch(args, w):
            "config": {"workload": w.name, "instances": m, "n_range": [min(ns), max(ns)], "starts_per_instance": k,
                       "iters": w.iters, "tenure": "[0.9n, 1.1n]", "graph": True,
                       "tile_rows_per_instance": rows_hist, "tuning_s": tune_s,
+                      "searches_in_block_form": k * sum(in_block),
                       "searches_per_variant": dict(zip(["r2_512", "r4_512", "r8_512", "stream_512", "r2_128",
                                                         "r2_256", "r4_256", "r4_768", "wide_512"],
-                                                       map(int, b.groups(counts=True)[1])))},
+                                                       map(int, tile_searches)))},
            "solves_per_s": m * k / (ms_step / 1e3), "table_kernel_ms": table_ms, "roofline": roof}
 
     if not args.no_plain:
@@ -517,16 +532,17 @@ def main():
     kname = ("search_kernel<%d,%s>" % (rows, "true" if algo == "tabu" else "false") if rows > 0 else
              "stream_kernel<%s,false,%s>" % ("true" if algo == "tabu" else "false",
                                              "true" if n > 256 else "false"))
-    if not args.tile_rows:
+    block = h.block_form(algo, lo, hi)
+    if block:
         kname = "wide_block_kernel" if n > 256 else "block_kernel"
-    roof = roofline(search_evals, search_ms, kname, traffic_for(w.name), algo, not args.tile_rows)
+    roof = roofline(search_evals, search_ms, kname, traffic_for(w.name), algo, search_evals if block else 0)
 
     out = {"metric": METRIC, "value": value, "unit": "evals/s", "n_gpus": 1, "steps": args.steps,
            "warmup": args.warmup, "ms_per_step": ms_step, "higher_is_better": True, "scaling": "weak",
            "vs_baseline": None, "dtype": "int32", "data": "synthetic",
            "config": {"workload": w.name, "n": n, "starts": k, "iters": w.iters,
-                      "tenure": [lo, hi] if algo == "tabu" else None, "tile_rows": rows,
-                      "lanes_per_search": lanes},
+                      "tenure": [lo, hi] if algo == "tabu" else None, "block_form": block,
+                      "tile_rows": None if block else rows, "lanes_per_search": None if block else lanes},
            "solves_per_s": solves, "table_kernel_ms": table_ms, "roofline": roof}
 
     if algo == "tabu" and not args.no_plain:

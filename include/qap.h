@@ -444,11 +444,16 @@ int qap_set_tile_rows(qap_handle h, int32_t algo, int32_t rows);
  * span at most 127, and tenures with hi - lo < 64 and hi <= 1000; above n = 256 single-instance
  * launches without the frequency memory with hi - lo < 128.  Every other search runs in tiles.
  * Results do not depend on the form.  qap_get_tile_rows and qap_launch_tile_rows report the
- * tile shape of the searches that run in tiles.
+ * tile shape of the searches that run in tiles; qap_block_form says which do.
  * qap_prefer_tile_rows is qap_set_tile_rows for the searches in tiles only: the block form
  * keeps what it serves.  It is the state qap_tune_tile_rows leaves behind.
  */
 int qap_prefer_tile_rows(qap_handle h, int32_t algo, int32_t rows);
+
+/* 1 if searches of algo (as above) with tenures in [lo, hi] (ignored for 2opt) and without the
+ * frequency memory run in block form as the handle's shapes now stand, 0 if in tiles.
+ * QAP_E_INVALID for bad arguments. */
+int qap_block_form(qap_handle h, int32_t algo, int32_t lo, int32_t hi);
 
 /* Tile rows currently used for algo, and the lanes per search in *lanes_out (may be
  * NULL); in the automatic mode, the shape of a launch of one start.  Same as

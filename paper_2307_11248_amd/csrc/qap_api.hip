@@ -623,6 +623,17 @@ int qap_get_tile_rows(qap_handle h, int32_t algo, int32_t *lanes_out) {
     return qap_launch_tile_rows(h, algo, 1, lanes_out);
 }
 
+int qap_block_form(qap_handle h, int32_t algo, int32_t lo, int32_t hi) {
+    if (!h || algo < 0 || algo > 2 || (algo != 1 && !tenure_args_ok(0, lo, hi))) return QAP_E_INVALID;
+    if (h->n <= WIDE_N) return use_block(h, algo, lo, hi) ? 1 : 0;
+    if (algo == 2 || !h->block_on[algo] || !h->stream_ok) return 0;
+    SearchArgs a = base_args(h, kStream);
+    a.lo = lo;
+    a.hi = hi;
+    a.tile_stride = stream_tile_int4(a.ntiles);
+    return wide_block_ok(algo == 0, a, h->max_smem);
+}
+
 int qap_launch_tile_rows(qap_handle h, int32_t algo, int32_t k, int32_t *lanes_out) {
     if (!h || algo < 0 || algo > 2 || k < 1) return QAP_E_INVALID;
     if (h->rows_choice[algo] < 0) return QAP_E_UNSUPPORTED;

@@ -34,7 +34,7 @@ EXPORTS = [
     "qap_strerror", "qap_create", "qap_destroy", "qap_size", "qap_cost", "qap_cost_async", "qap_delta_table",
     "qap_delta_table_async", "qap_2opt", "qap_2opt_async", "qap_tabu", "qap_tabu_async", "qap_tabu_noalloc_async",
     "qap_tabu_freq_async", "qap_tabu_trace_async",
-    "qap_tabu_plain_async", "qap_2opt_with_table_async", "qap_tabu_with_table_async", "qap_set_tile_rows", "qap_prefer_tile_rows",
+    "qap_tabu_plain_async", "qap_2opt_with_table_async", "qap_tabu_with_table_async", "qap_set_tile_rows", "qap_prefer_tile_rows", "qap_block_form",
     "qap_get_tile_rows", "qap_launch_tile_rows", "qap_batch_create", "qap_batch_create_freq", "qap_batch_freq_async", "qap_batch_size", "qap_batch_groups",
     "qap_batch_run_async",
     "qap_batch_tables_async", "qap_batch_search_async", "qap_batch_destroy", "qap_tabu_batch",
@@ -97,6 +97,7 @@ def lib():
                                                              _vp, _vp]),
                 "qap_set_tile_rows": (ctypes.c_int, [_vp, i32, i32]),
                 "qap_prefer_tile_rows": (ctypes.c_int, [_vp, i32, i32]),
+                "qap_block_form": (ctypes.c_int, [_vp, i32, i32, i32]),
                 "qap_get_tile_rows": (ctypes.c_int, [_vp, i32, _i32p]),
                 "qap_launch_tile_rows": (ctypes.c_int, [_vp, i32, i32, _i32p]),
                 "qap_tune_tile_rows": (ctypes.c_int, [_vp, i32, i32, i32, ctypes.POINTER(ctypes.c_float)]),
@@ -228,6 +229,10 @@ class Handle:
         """The tile shape of the searches that run in tiles; the block form keeps the others
         (``qap_prefer_tile_rows``)."""
         _check(lib().qap_prefer_tile_rows(self.ptr, ALGOS[algo], int(rows)), "qap_prefer_tile_rows")
+
+    def block_form(self, algo: str, lo: int = 0, hi: int = 0) -> bool:
+        """Whether searches of algo with tenures in [lo, hi] run in block form (``qap_block_form``)."""
+        return _check(lib().qap_block_form(self.ptr, ALGOS[algo], int(lo), int(hi)), "qap_block_form") == 1
 
     def tile_rows(self, algo: str):
         lanes = ctypes.c_int32(0)

@@ -54,3 +54,30 @@ def test_batch_groups_are_the_kernels_that_run():
         assert b.starts - c.sum() == sum(kk for kk, case in zip(k, cases) if isinstance(case[-1], str))
     for h in hs:
         h.close()
+
+
+# the limits of the block form: spans, tenures, n, the shapes set on the handle
+def test_block_form_says_which_searches_it_runs():
+    note("block form query")
+    for n, wide in ((60, 64), (256, 64), (257, 128), (512, 128)):
+        with qap.Handle(*instance(n)) as h:
+            assert h.block_form("tabu", 10, 20) and h.block_form("2opt")
+            assert h.block_form("batch", 10, 20) == (n <= 256)
+            assert h.block_form("tabu", 10, 10 + wide - 1) and not h.block_form("tabu", 10, 10 + wide)
+            assert h.block_form("tabu", 1000, 1000) and not h.block_form("tabu", 1001, 1001)
+            rows = h.tile_rows("tabu")[0]
+            h.set_tile_rows("tabu", rows)
+            assert not h.block_form("tabu", 10, 20) and h.block_form("2opt")
+            h.prefer_tile_rows("tabu", rows)
+            assert h.block_form("tabu", 10, 20)
+            h.set_tile_rows("2opt", h.tile_rows("2opt")[0])
+            assert not h.block_form("2opt")
+            h.set_tile_rows("2opt", 0)
+            assert h.block_form("2opt")
+            for args in (("tabu", -1, 5), ("tabu", 6, 5), ("batch", 6, 5)):
+                with pytest.raises(qap.QapError) as ei:
+                    h.block_form(*args)
+                assert ei.value.code == qap.QAP_E_INVALID
+        for spans, block in (((127, 255), True), ((255, 127), True), ((128, 255), False), ((255, 255), False)):
+            with qap.Handle(*instance(n, False, *spans)) as h:
+                assert h.block_form("tabu", 10, 20) == block and h.block_form("2opt") == block, (n, spans)
