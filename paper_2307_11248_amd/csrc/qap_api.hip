@@ -82,13 +82,14 @@ int dev_err_at(hipError_t e, const char *where) {
 
 // Side streams a batched launch forks into: one fewer than the hardware queues HIP gives
 // the process (GPU_MAX_HW_QUEUES, 4 unless set), so that each lane has a queue of its own
-// beside the caller's stream; QAP_BATCH_LANES overrides the count.
-static int side_lanes() {
+// beside the caller's stream; QAP_BATCH_LANES overrides the count (*forced_out).
+static int side_lanes(bool *forced_out) {
     auto env_int = [](const char *name, int dflt) {
         const char *v = std::getenv(name);
         return v && *v ? std::atoi(v) : dflt;
     };
     const int forced = env_int("QAP_BATCH_LANES", 0);
+    *forced_out = forced > 0;
     const int lanes = forced > 0 ? forced : env_int("GPU_MAX_HW_QUEUES", 4) - 1;
     return std::max(1, std::min(lanes, (int)BV_COUNT));
 }
@@ -437,6 +438,8 @@ struct WideTable {
 
 // Kernel variants of a batch: the tile shapes, then the block form's kernels.
 constexpr int GV_COUNT = BV_COUNT + BLOCK_FORMS;
+// Below this estimate (us) a plan's kernels run one after another, not side by side.
+constexpr double kForkUs = 60;
 
 struct qap_batch {
     int count = 0;                  // searches (items)
@@ -455,11 +458,12 @@ struct qap_batch {
     size_t group_smem[GV_COUNT] = {};
     bool busy = false;              // more searches than compute units
     int narrow = 0;                 // items of the tile shapes up to WIDE_N (they come first)
-    // The groups run on `nlanes` side streams forked from the caller's stream, the groups
-    // of one lane back to back: lane_groups[lane_begin[l] .. lane_begin[l + 1]).  Streams
-    // beyond the device's hardware queues would share queues, and kernels on one queue
-    // run in order, so there are at most as many lanes as free queues; the groups are
-    // dealt to them by estimated work, largest first, each to the least loaded lane.
+    // The groups run on `nlanes` lanes, the groups of one lane back to back: lane_groups[
+    // lane_begin[l] .. lane_begin[l + 1]).  Lane 0 is the caller's stream, the others are side
+    // streams forked from it and joined back.  Streams beyond the device's hardware queues
+    // would share queues, and kernels on one queue run in order, so there are at most as many
+    // lanes as free queues; the groups are dealt to them by estimated work, largest first,
+    // each to the least loaded lane.
     int nlanes = 0;
     int lane_begin[GV_COUNT + 1] = {};
     int lane_groups[GV_COUNT] = {};
@@ -1061,7 +1065,22 @@ int batch_create_impl(const qap_handle *hs, int32_t m, const int32_t *k_per, int
     }
     std::stable_sort(order, order + GV_COUNT, [&](int x, int y) { return work[x] > work[y]; });
     if (!freq && ngroups > 0) {
-        b->nlanes = std::min(ngroups, side_lanes());
+        bool forced = false;
+        b->nlanes = std::min(ngroups, side_lanes(&forced));
+        // How much later the plan ends with its groups one after another: every group's time but
+        // the longest's, about 1 us an iteration in block form up to n = 64 (n / 64 above), twice
+        // that in tiles, for every round over the compute units.  A side stream costs 33 us with
+        // the plan and two events of 17 us each run, so below kForkUs there is one lane (two
+        // searches of n = 8 and 9, one iteration, plan included: 284 us with two side streams).
+        double sum = 0, most = 0;
+        for (int g = 0; g < ngroups; ++g) {
+            const int v = order[g];
+            const double us = (v < BV_COUNT ? 2.0 : 1.0) * iters * std::max(1.0, items[b->group_begin[v]].n / 64.0) *
+                              ((b->group_count[v] + hs[0]->cus - 1) / hs[0]->cus);
+            sum += us;
+            most = std::max(most, us);
+        }
+        if (!forced && sum - most < kForkUs) b->nlanes = 1;
         long long load[GV_COUNT] = {};
         int lane_of[GV_COUNT], per_lane[GV_COUNT] = {};
         for (int g = 0; g < ngroups; ++g) {   // largest first, each to the least loaded lane
@@ -1101,7 +1120,7 @@ int batch_create_impl(const qap_handle *hs, int32_t m, const int32_t *k_per, int
     hipError_t e = hipSuccess;
     if (b->nlanes > 1) {
         e = hipEventCreateWithFlags(&b->ev_fork, hipEventDisableTiming);
-        for (int l = 0; l < b->nlanes && e == hipSuccess; ++l) {
+        for (int l = 1; l < b->nlanes && e == hipSuccess; ++l) {
             e = hipStreamCreateWithFlags(&b->side[l], hipStreamNonBlocking);
             if (e == hipSuccess) e = hipEventCreateWithFlags(&b->ev_join[l], hipEventDisableTiming);
         }
@@ -1205,8 +1224,8 @@ extern "C" int qap_batch_search_async(qap_batch_handle b, int32_t *d_perms, int6
     const bool fork = b->nlanes > 1;
     hipError_t e = fork ? hipEventRecord(b->ev_fork, st) : hipSuccess;
     for (int l = 0; l < b->nlanes && e == hipSuccess; ++l) {
-        hipStream_t ls = fork ? b->side[l] : st;
-        if (fork) e = hipStreamWaitEvent(ls, b->ev_fork, 0);
+        hipStream_t ls = l == 0 ? st : b->side[l];
+        if (l > 0) e = hipStreamWaitEvent(ls, b->ev_fork, 0);
         for (int g = b->lane_begin[l]; g < b->lane_begin[l + 1] && e == hipSuccess; ++g) {
             const int v = b->lane_groups[g];
             BatchArgs a{b->d_items + b->group_begin[v], b->group_count[v], d_perms, d_best, d_done, b->d_table,
@@ -1216,11 +1235,11 @@ extern "C" int qap_batch_search_async(qap_batch_handle b, int32_t *d_perms, int6
             else
                 e = launch_batch_group(v, a, b->group_smem[v], ls);
         }
-        if (fork && e == hipSuccess) e = hipEventRecord(b->ev_join[l], ls);
+        if (l > 0 && e == hipSuccess) e = hipEventRecord(b->ev_join[l], ls);
     }
     // the joins after every lane's launches, so that no wait of the caller's stream sits
     // in a hardware queue ahead of a lane's kernels
-    for (int l = 0; fork && l < b->nlanes && e == hipSuccess; ++l) e = hipStreamWaitEvent(st, b->ev_join[l], 0);
+    for (int l = 1; l < b->nlanes && e == hipSuccess; ++l) e = hipStreamWaitEvent(st, b->ev_join[l], 0);
     return dev_err(e);
 }
 
