@@ -77,6 +77,7 @@ hipError_t hipMemsetAsync(void *d, int v, size_t n, hipStream_t st) {
     return e;
 }
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) {
+    if (fails()) return hipErrorUnknown;
     Stream *st = new Stream;
     st->id = (int)g_streams.size();
     g_streams.push_back(st);
