@@ -1072,11 +1072,12 @@ int batch_create_impl(const qap_handle *hs, int32_t m, const int32_t *k_per, int
         // that in tiles, for every round over the compute units.  A side stream costs 33 us with
         // the plan and two events of 17 us each run, so below kForkUs there is one lane (two
         // searches of n = 8 and 9, one iteration, plan included: 284 us with two side streams).
+        const int cus = std::max(1, hs[0]->cus);
         double sum = 0, most = 0;
         for (int g = 0; g < ngroups; ++g) {
             const int v = order[g];
             const double us = (v < BV_COUNT ? 2.0 : 1.0) * iters * std::max(1.0, items[b->group_begin[v]].n / 64.0) *
-                              ((b->group_count[v] + hs[0]->cus - 1) / hs[0]->cus);
+                              ((b->group_count[v] + cus - 1) / cus);
             sum += us;
             most = std::max(most, us);
         }
