@@ -8,7 +8,8 @@ the fastest.  The time depends on n, on whether F and D are both symmetric, and 
 algorithm, not on the matrix values (a tabu search does the same work every iteration),
 so one measurement serves every instance with the same key, and the cache keeps it
 across processes.  The key also names the GPU architecture and a digest of the built
-library, so a rebuilt kernel is tuned again.
+library, so a rebuilt kernel is tuned again.  Searches in block form have no tile shape
+(``Handle.block_form`` says which those are): a tuned one is for the others.
 """
 from __future__ import annotations
 

@@ -43,8 +43,11 @@
 // The rows and columns of r and s in the blocks are stale between B and the next A and are
 // left out of the blocks' minimum; the task waves' candidates stand for them.
 //
-// Bound by the chain of an iteration (two barriers, about 0.9 us up to n = 96), from n = 160 on
-// also by the task waves' LDS reads (2 n^2 bytes for each of rows and columns).  us per
+// Bound by the chain of an iteration (two barriers, about 0.9 us up to n = 96), from n = 160 on by
+// the task waves' waits for LDS.  At n = 256 their reads (2 n^2 bytes for each of rows and
+// columns, 128 a clock) and products are 0.85 and 0.5 us of 3.5: a wave of two groups (TC = 2)
+// asks for the operands of a half step, waits and multiplies, eight times, with nothing of the
+// next half step on its way (waves wait 0.55 of their cycles and issue in 0.25).  us per
 // iteration, tiles (qap_search.hip) and here, one search a compute unit: n = 40 2.0 and 1.0,
 // n = 64 1.9 and 0.9, n = 128 symmetric 2.4 and 1.2, n = 256 17.7 and 3.5; 4096 searches of
 // uneven n up to 150: 29.6 and 16.7 ms for 1000 iterations.

@@ -5,8 +5,9 @@
 // footprint fits the server's memory pool; a request that does not fit is passed over
 // by later ones that do, until it has been passed over kMaxPassOvers times, after which
 // nothing behind it is admitted before it (so a large request cannot starve).  Each step
-// runs one chunk of every admitted search in a single launch (one workgroup per search,
-// each stopping at an iteration boundary once a clock budget is spent) and keeps the
+// runs one chunk of every admitted search (one workgroup per search, each stopping at an
+// iteration boundary once a clock budget is spent; one launch for each kernel in use, side
+// by side on forked streams, waited for before the step returns) and keeps the
 // search's permutation, tabu list and neighbourhood on the device between chunks, so a
 // search gives exactly the result it gives when run alone in one go.  Requests that
 // arrive while a chunk runs join at the next step; finished searches free their slot and

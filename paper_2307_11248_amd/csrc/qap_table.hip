@@ -187,9 +187,9 @@ __device__ inline long long tb_load8(const uint8_t *p) { return *reinterpret_cas
 // TW_KC: each chunk stages X and Y of both row blocks (X gathered from global F through
 // the permutation, Y read from global D, both shifted to int8), adds its part of the row
 // sums and diagonal terms of those rows, and accumulates the 32 x 32 output tiles of the
-// pair (two per wave) with v_mfma_i32_32x32x16_i8.  The epilogue is the one of the
-// single-block kernel, with the entries of D and G at (i, j), (j, i), (i, i), (j, j)
-// read from global memory.  Bound by the gathers of X: four go out at once, without a branch,
+// pair (two per wave) with v_mfma_i32_32x32x16_i8.  The epilogue undoes the
+// shift from the row sums and adds the k = i, j terms one by one, with the entries of D and G
+// at (i, j), (j, i), (i, i), (j, j) read from global memory.  Bound by the gathers of X: four go out at once, without a branch,
 // beside one word of Y (entry by entry, each behind its test, 256 starts at n = 512 took 860
 // us, symmetric 516, 64 at n = 300 122; now 622, 402 and 87).
 
