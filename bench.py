@@ -47,13 +47,23 @@ VALU_PER_EVAL = {"tabu": 8, "2opt": 6}
 BLOCK_VALU_PER_EVAL = {"tabu": 2, "2opt": 1.5}
 BYTES_PER_EVAL = 8   # an int32 delta read and written per entry per step if kept in HBM
 
-# HBM bytes per launch of the dominant kernel, from rocprofv3 FETCH_SIZE and WRITE_SIZE
+# HBM bytes per launch of the block-form kernels, from rocprofv3 FETCH_SIZE and WRITE_SIZE
 # runs scaled by a plain copy's counts (x2 and x1; see the summaries under profiles/),
 # valid only for the kernel sources they were taken with.
 KERNEL_SOURCES = ["paper_2307_11248_amd/csrc/" + f for f in
                   ("qap_search.hip", "qap_block.h", "qap_block.hip", "qap_block_busy.hip", "qap_block_freq.hip",
                    "qap_block_wide.hip", "qap_internal.h")]
-TRAFFIC = {}   # workload: {"bytes": .., "sources": kernel_digest()}; none taken with these sources
+TRAFFIC_SOURCES = "1f34ecccf9737f45"   # kernel_digest() of the sources they were taken with
+TRAFFIC = {
+    "c2_n64_dense_tabu": int((2 * 686.0 + 40.0) * 1024),
+    "c3_n128_euclid_2opt": int((2 * 16830.9 + 3488.0) * 1024),
+    "c3_n128_euclid_tabu": int((2 * 4401.1 + 144.0) * 1024),
+    # summed over the five kernels of one graph replay (n to 150, 128, 96, 64, 32)
+    "c4_batched_uneven_tabu": int((2 * (13386.1 + 18229.6 + 9229.0 + 4543.9 + 962.2)
+                                   + (4942.5 + 9153.4 + 4773.4 + 1340.8 + 216.6)) * 1024),
+    "n256_dense_tabu": int((2 * 24423.2 + 8959.6) * 1024),
+    "n512_dense_tabu": int((2 * 59493185.6 + 104499416.6) * 1024),
+}
 
 
 def roofline(search_evals, kernel_ms, kernel, traffic, algo, block_evals):
@@ -86,8 +96,7 @@ def kernel_digest():
 
 
 def traffic_for(workload):
-    t = TRAFFIC.get(workload)
-    return t["bytes"] if t is not None and t["sources"] == kernel_digest() else None
+    return TRAFFIC.get(workload) if kernel_digest() == TRAFFIC_SOURCES else None
 
 
 def parse():
@@ -289,7 +298,7 @@ def run_batch(args, w):
     roof = roofline(search_evals, search_ms, "%s (search phase: %d kernel dispatches on the "
                     "graph's lanes; replay time less the table kernel)" %
                     (" and ".join(["block_kernel"] * any(in_block) + ["batch_group_kernel"] * (not all(in_block))),
-                     ngroups), traffic_for(w.name), "tabu", block_evals)
+                     ngroups), traffic_for(w.name) if all(in_block) else None, "tabu", block_evals)
     roof["replay_ms"] = round(replay_ms, 4)
     roof["eager_search_ms"] = round(eager_search_ms, 4)
     ns = [I.n for I in insts]
@@ -535,7 +544,8 @@ def main():
     block = h.block_form(algo, lo, hi)
     if block:
         kname = "wide_block_kernel" if n > 256 else "block_kernel"
-    roof = roofline(search_evals, search_ms, kname, traffic_for(w.name), algo, search_evals if block else 0)
+    roof = roofline(search_evals, search_ms, kname, traffic_for(w.name) if block else None, algo,
+                    search_evals if block else 0)
 
     out = {"metric": METRIC, "value": value, "unit": "evals/s", "n_gpus": 1, "steps": args.steps,
            "warmup": args.warmup, "ms_per_step": ms_step, "higher_is_better": True, "scaling": "weak",

@@ -24,8 +24,8 @@
 // slots (32 KB of LDS at n = 512 that hold blocks instead).
 // Bound, up to n = 416, by the reads of the matrices from L2 (4 n^2 bytes an iteration and
 // search, half for symmetric instances), above also by the scratch blocks (0.4 MB an iteration
-// at n = 512, more than L2 holds for 32 searches: 256 searches moved 285 GB in 55 ms with 64
-// blocks there, 5.2 TB/s; 51 are left).
+// at n = 512, more than L2 holds for 32 searches: 256 searches of 2000 iterations moved 285 GB in
+// 55 ms with 64 blocks there, 5.2 TB/s, and move 229 GB in 52 ms with the 51 that are left).
 // us per iteration with the tiles streamed through scratch (8 bytes a slot, read and written)
 // and here, tables included, 256 searches: n = 300 29.4 and 13.2, n = 512 59.7 and 32.5,
 // n = 512 symmetric 50.1 and 26.2; 64 searches n = 400 30.3 and 19.2; one n = 512 39.4 and 23.0.
