@@ -1224,9 +1224,11 @@ extern "C" int qap_batch_search_async(qap_batch_handle b, int32_t *d_perms, int6
     }
     const bool fork = b->nlanes > 1;
     hipError_t e = fork ? hipEventRecord(b->ev_fork, st) : hipSuccess;
+    int started = 0;
     for (int l = 0; l < b->nlanes && e == hipSuccess; ++l) {
         hipStream_t ls = l == 0 ? st : b->side[l];
         if (l > 0) e = hipStreamWaitEvent(ls, b->ev_fork, 0);
+        if (e == hipSuccess) started = l + 1;
         for (int g = b->lane_begin[l]; g < b->lane_begin[l + 1] && e == hipSuccess; ++g) {
             const int v = b->lane_groups[g];
             BatchArgs a{b->d_items + b->group_begin[v], b->group_count[v], d_perms, d_best, d_done, b->d_table,
@@ -1241,6 +1243,9 @@ extern "C" int qap_batch_search_async(qap_batch_handle b, int32_t *d_perms, int6
     // the joins after every lane's launches, so that no wait of the caller's stream sits
     // in a hardware queue ahead of a lane's kernels
     for (int l = 1; l < b->nlanes && e == hipSuccess; ++l) e = hipStreamWaitEvent(st, b->ev_join[l], 0);
+    // what failed may have started lanes: whoever waits for the caller's stream waits for them too
+    for (int l = 1; l < started && e != hipSuccess; ++l)
+        if (hipEventRecord(b->ev_join[l], b->side[l]) == hipSuccess) (void)hipStreamWaitEvent(st, b->ev_join[l], 0);
     return dev_err(e);
 }
 

@@ -46,8 +46,9 @@ int stream_shape_ok(int, int, size_t) { return 1; }
 namespace {
 
 // A plan of one search for each size (odd ones symmetric), run once.  Returns the streams it
-// created, -1 if something failed or was not finished with the caller's stream.
-int plan(const std::vector<int> &sizes, int iters, int copies = 1) {
+// created, -1 if something failed or was not finished with the caller's stream.  fail_at: the
+// call of the run that fails, counted from 0.
+int plan(const std::vector<int> &sizes, int iters, int copies = 1, int fail_at = -1) {
     std::vector<qap_handle> hs;
     std::vector<int32_t> k, lo, hi, perms;
     std::vector<uint64_t> seed;
@@ -72,7 +73,12 @@ int plan(const std::vector<int> &sizes, int iters, int copies = 1) {
     qap_batch_size(b, &starts, &ints);
     std::vector<int32_t> p(ints), done(starts);
     std::vector<int64_t> best(starts);
+    g_calls = 0;
+    g_failed = false;
+    g_fail_at = fail_at;
     int rc = qap_batch_run_async(b, p.data(), best.data(), done.data(), st);
+    g_fail_at = -1;
+    if (g_failed) rc = rc == 0 ? -1 : 0;   // a failed call fails the run
     (void)hipStreamSynchronize(st);
     if (!idle()) rc = -1;
     qap_batch_destroy(b);
@@ -94,5 +100,14 @@ int main() {
     std::printf("%d\n", plan({8, 9}, 30, 1000));                 // many rounds over the compute units
     setenv("QAP_BATCH_LANES", "2", 1);
     std::printf("%d\n", plan({8, 9, 100}, 1));                   // as told
+    unsetenv("QAP_BATCH_LANES");
+    // every call of a run on three lanes failing in turn
+    int bad = 0, fail = 0;
+    for (;; ++fail) {
+        const int r = plan({20, 31, 40, 51, 60, 91, 200, 300}, 2000, 1, fail);
+        if (r < 0) ++bad, std::fprintf(stderr, "call %d failed\n", fail);
+        if (!g_failed) break;
+    }
+    std::printf("%d\n%d\n", bad, fail);
     return 0;
 }
